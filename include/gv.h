@@ -76,8 +76,11 @@ enum { GV_MAP_UNIFORM = 0, GV_MAP_SOLENOID = 1 };
  * atomic add per queue), so queue order across baskets follows completion
  * order; within a basket it is slot order.  STABLE: output order is the
  * order of the input slots (single-pass look-back over the claimed baskets),
- * identical in every run.  Results are the same in both: a track's random
- * numbers are keyed by (event, track id, step), never by its queue slot. */
+ * identical in every run.  Populations too small to fill the GPU, of
+ * transports that leave every knob at 0 and record no steps, are followed in
+ * on-chip pools instead, which have no such order.  Results are the same in
+ * all: a track's random numbers are keyed by (event, track id, step), never by
+ * its queue slot. */
 enum { GV_ORDER_ARRIVAL = 0, GV_ORDER_STABLE = 1 };
 /* Accumulation of deposits and of the energy ledger.  FLOAT: FP64 atomic
  * adds, whose sums depend on arrival order in the last bits.  FIXED: each
@@ -171,7 +174,9 @@ typedef struct {
                                        of >= 4096 primaries (trial transports of a sample of
                                        the batch, choice cached per precision, order and batch
                                        size class), otherwise they take the defaults
-                                       256 / 3 / 4 */
+                                       256 / 3 / 4.  With all knobs and graph_steps and
+                                       capacity at 0 and no trace, populations too small to
+                                       fill the GPU run in the pool kernel, which has none */
     int32_t graph_steps;            /* step launches per captured graph, 0 = default */
     int32_t field_method;           /* GV_FIELD_HELIX, GV_FIELD_RK4 or GV_FIELD_RK45 */
     int32_t edep_on_device;         /* edep_out of gv_transport is a device pointer */

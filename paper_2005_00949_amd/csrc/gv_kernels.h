@@ -629,7 +629,7 @@ struct Ctrl {
     uint32_t overflow;      // bit 0: a queue ran out of capacity; bit 1: a look-back wait gave up
     uint32_t done;          // workgroups finished in this launch
     uint32_t halt;          // overflow as seen at the end of the previous launch
-    uint32_t pad;
+    uint32_t n_vac;         // pool kernel: charged tracks in vacuum among this launch's outputs
     uint64_t seed;          // run seed (device-resident so captured graphs are reusable)
     // integration queue, on a cache line of its own (every wavefront that
     // parks a move adds to it): moves parked in this launch per charged type,
@@ -736,13 +736,25 @@ __global__ void k_ingest(const PrimDev* prim, long long n, const uint32_t* slot,
     if (q.type) q.type[k] = (int8_t)p.type;
 }
 
+// What the host reads between launches of the pool kernel, in pinned host
+// memory: the last workgroup of a launch writes it, so no copy is enqueued.
+struct CtrlMirror {
+    uint32_t count[3];          // tracks queued for the next launch, by type
+    uint32_t n_vac;             // of them, charged tracks in vacuum
+    uint32_t overflow;
+    uint32_t pad;
+    unsigned long long steps;   // steps of the transport so far
+};
+
 // end of a launch, run by the last of the `participants` workgroups to
 // finish: the consumed input counts become the next launch's (empty) output,
 // the basket ticket restarts and the look-back epoch advances.  Every
 // participant has read the control block before it increments `done`, and
 // the other workgroups left without touching it, so nothing reads these words
 // afterwards.
-__device__ __forceinline__ void finish_launch(Ctrl* ctrl, int parity, uint32_t participants)
+__device__ __forceinline__ void finish_launch(Ctrl* ctrl, int parity, uint32_t participants,
+                                              CtrlMirror* mirror = nullptr,
+                                              const unsigned long long* counters = nullptr)
 {
     __threadfence();
     __syncthreads();
@@ -750,6 +762,19 @@ __device__ __forceinline__ void finish_launch(Ctrl* ctrl, int parity, uint32_t p
         const uint32_t d = atomicAdd(&ctrl->done, 1u);
         if (d == participants - 1) {
             __threadfence();
+            if (mirror) {
+                // counts and counters were added to by other XCDs: read past this one's L2
+                for (int t = 0; t < 3; ++t)
+                    mirror->count[t] = __hip_atomic_load(&ctrl->count[parity ^ 1][t], __ATOMIC_RELAXED,
+                                                         __HIP_MEMORY_SCOPE_AGENT);
+                mirror->n_vac = __hip_atomic_load(&ctrl->n_vac, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                mirror->overflow = __hip_atomic_load(&ctrl->overflow, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                unsigned long long steps = 0;
+                for (int t = 0; t < 3; ++t)
+                    steps += __hip_atomic_load(&counters[kCSteps + t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                mirror->steps = steps;
+                ctrl->n_vac = 0;
+            }
             ctrl->count[parity][0] = 0;
             ctrl->count[parity][1] = 0;
             ctrl->count[parity][2] = 0;

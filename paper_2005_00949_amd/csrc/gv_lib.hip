@@ -27,6 +27,7 @@
 #include <vector>
 
 #include "gv_kernels.h"
+#include "gv_pool.h"
 
 using namespace gv;
 
@@ -146,6 +147,7 @@ struct Lib {
     bool busy = false;
     int device = -1;
     int n_cu = 256;
+    int wall_khz = 100000;   // rate of the device's wall clock
     hipStream_t own_stream = nullptr;
     gv_config cfg{};
     DevGeom geom{};
@@ -181,6 +183,7 @@ struct Lib {
     DBuf<PrimDev> prim;
     DBuf<uint32_t> prim_slot;
     Ctrl* h_ctrl = nullptr;  // pinned
+    CtrlMirror* h_mirror = nullptr;  // pinned, written by the pool kernel
     hipGraphExec_t gexec = nullptr;      // bulk: full grid, bulk inner steps
     hipGraph_t graph = nullptr;
     hipGraphExec_t gexec_tail = nullptr; // tail: small grid, tail inner steps
@@ -296,6 +299,8 @@ void release_all()
     L.prim_slot.release();
     if (L.h_ctrl) (void)hipHostFree(L.h_ctrl);
     L.h_ctrl = nullptr;
+    if (L.h_mirror) (void)hipHostFree(L.h_mirror);
+    L.h_mirror = nullptr;
     if (L.ev0) (void)hipEventDestroy(L.ev0);
     if (L.ev1) (void)hipEventDestroy(L.ev1);
     L.ev0 = L.ev1 = nullptr;
@@ -536,6 +541,7 @@ int ensure_common(int64_t n_events)
     }
     HIPCHK(L.snap.ensure(kNCount + kEhSize + 1));
     if (!L.h_ctrl) HIPCHK(hipHostMalloc((void**)&L.h_ctrl, sizeof(Ctrl), hipHostMallocDefault));
+    if (!L.h_mirror) HIPCHK(hipHostMalloc((void**)&L.h_mirror, sizeof(CtrlMirror), hipHostMallocDefault));
     if (!L.ev0) HIPCHK(hipEventCreate(&L.ev0));
     if (!L.ev1) HIPCHK(hipEventCreate(&L.ev1));
     return GV_OK;
@@ -629,6 +635,7 @@ int upload_ctrl(const uint32_t counts[3], uint64_t seed)
     c.count[0][3] = c.count[1][3] = 0;
     c.rk_split[0] = c.rk_split[1] = 0ull;
     c.rk_grab = c.rk_ticket = c.rk_done = 0;
+    c.n_vac = 0;
     c.ticket = 0;
     c.overflow = 0;
     c.done = 0;
@@ -836,16 +843,10 @@ template <class P> int build_graph(const Tuning& tu, const GraphKey& key)
     return GV_OK;
 }
 
-// batched transport of one event window; returns GV_E_CAPACITY on overflow
-template <class P> int run_batched_window(size_t b, size_t e, uint64_t seed, const Tuning& tu)
+// the step kernel's graphs for the current options, captured if they are not there
+template <class P> int ensure_bulk_graph(const Tuning& tu)
 {
     QueueMem<P>& Q = batch_queues<P>();
-    L.tail_steps0 = 0;
-    uint32_t counts[3];
-    int rc = ingest<P>(b, e, Q.q[0], counts, Q.cap, false);
-    if (rc) return rc;
-    rc = upload_ctrl(counts, seed);
-    if (rc) return rc;
     GraphKey key;
     key.prec = P::kMixed ? GV_PMIX : GV_P64;
     key.block = tu.block;
@@ -865,10 +866,22 @@ template <class P> int run_batched_window(size_t b, size_t e, uint64_t seed, con
     key.grid = tu.occupancy * L.n_cu;
     key.tail_grid = tu.tail_grid;
     key.tail_K = tu.tail_K;
-    if (!L.gexec || !(L.gkey == key)) {
-        rc = build_graph<P>(tu, key);
-        if (rc) return rc;
-    }
+    if (L.gexec && L.gkey == key) return GV_OK;
+    return build_graph<P>(tu, key);
+}
+
+// batched transport of one event window; returns GV_E_CAPACITY on overflow
+template <class P> int run_batched_window(size_t b, size_t e, uint64_t seed, const Tuning& tu)
+{
+    QueueMem<P>& Q = batch_queues<P>();
+    L.tail_steps0 = 0;
+    uint32_t counts[3];
+    int rc = ingest<P>(b, e, Q.q[0], counts, Q.cap, false);
+    if (rc) return rc;
+    rc = upload_ctrl(counts, seed);
+    if (rc) return rc;
+    rc = ensure_bulk_graph<P>(tu);
+    if (rc) return rc;
     hipStream_t s = stream();
     uint32_t population = counts[0] + counts[1] + counts[2];
     uint32_t peak = population;
@@ -926,6 +939,156 @@ template <class P> int run_batched_window(size_t b, size_t e, uint64_t seed, con
         }
         if (launches > bound) return fail(GV_E_STATE, "step loop did not terminate within its launch bound");
     }
+    return GV_OK;
+}
+
+// ---- the pool kernel's driver ----------------------------------------------
+
+// The pool kernel takes part in transports whose knobs are all left to the
+// library: a caller that sets one asks for the step kernel it describes, a
+// trace records whole steps, and an explicit capacity bounds the step kernel's
+// queue use.
+bool pool_mode()
+{
+    const gv_config& c = L.cfg;
+    return c.driver == GV_DRIVER_BATCHED && c.trace_cap == 0 && c.capacity == 0 && !c.basket && !c.occupancy &&
+           !c.inner_steps && !c.graph_steps;
+}
+
+// Time a wavefront takes per launch once its input is used up (microseconds):
+// longer, and wavefronts that have emptied their pools wait for the others;
+// shorter, and launches and their read-backs (~25 us) weigh more (1000 x 10 GeV
+// e-: 17.2 / 16.5 / 16.2 ms at 50 / 100 / 200 us; 100 x 50 GeV with RK45: 115 /
+// 106 / 111 ms).  And steps a track takes per stage: 4 to 8 measured alike, 2
+// and 16 slower; with an integrator, whose steps may take a hundred times
+// longer, fewer.
+constexpr int kPoolBudget = 100;
+constexpr int kPoolInner = 8;
+constexpr int kPoolInnerInteg = 2;
+// vacuum steps per track and helper launch between two pool launches
+constexpr int kPoolHelperSteps = 16384;
+
+template <class P> void launch_pool(int parity, int grid, hipStream_t s)
+{
+    QueueMem<P>& Q = batch_queues<P>();
+    PoolArgs<P> A;
+    for (int t = 0; t < 3; ++t) {
+        A.in[t] = Q.q[parity][t];
+        A.out[t] = Q.q[parity ^ 1][t];
+    }
+    A.ctrl = L.ctrl.p;
+    A.mirror = L.h_mirror;
+    A.cap = (uint32_t)Q.cap;
+    A.parity = parity;
+    A.budget = (long long)kPoolBudget * L.wall_khz / 1000;
+    A.inner = L.cfg.field_method != GV_FIELD_HELIX ? kPoolInnerInteg : kPoolInner;
+    A.S = make_sinks();
+    A.tv = tab_view<typename P::R>();
+    if (L.cfg.field_method != GV_FIELD_HELIX) k_pool<P, true><<<grid, kPoolBlock, 0, s>>>(A);
+    else k_pool<P, false><<<grid, kPoolBlock, 0, s>>>(A);
+}
+
+template <class P> void launch_pool_helper(int parity, hipStream_t s)
+{
+    QueueMem<P>& Q = batch_queues<P>();
+    BatchArgs<P> A{};
+    for (int t = 0; t < 3; ++t) A.in[t] = Q.q[parity][t];
+    A.ctrl = L.ctrl.p;
+    A.cap = (uint32_t)Q.cap;
+    A.parity = parity;
+    A.S = make_sinks();
+    A.tv = tab_view<typename P::R>();
+    if (L.cfg.field_method != GV_FIELD_HELIX)
+        k_vacuum_helper<P, kHelperInteg><<<1, kVacHelperBlock, 0, s>>>(A, kVacHelperSteps);
+    else if (L.geom.field_map == kMapUniform)
+        k_vacuum_helper<P, kHelperLooper><<<1, kVacHelperBlock, 0, s>>>(A, kPoolHelperSteps);
+    else
+        k_vacuum_helper<P, kHelperHelix><<<1, kVacHelperBlock, 0, s>>>(A, kPoolHelperSteps);
+}
+
+// Batched transport of one event window with the pool kernel.  Populations
+// that fill the GPU (the tail threshold and above) run in the step kernel's
+// bulk graph, which starts and ends at parity 0; so pool launches come in
+// pairs.
+template <class P> int run_pool_window(size_t b, size_t e, uint64_t seed, const Tuning& tu)
+{
+    QueueMem<P>& Q = batch_queues<P>();
+    uint32_t counts[3];
+    int rc = ingest<P>(b, e, Q.q[0], counts, Q.cap, false);
+    if (rc) return rc;
+    rc = upload_ctrl(counts, seed);
+    if (rc) return rc;
+    hipStream_t s = stream();
+    const int grid_full = PoolSize<P>::wgs(L.cfg.field_method != GV_FIELD_HELIX) * L.n_cu;
+    uint32_t n = counts[0] + counts[1] + counts[2], peak = n, n_vac = 0;
+    uint32_t n_gamma = counts[0];
+    bool grew = true, in_tail = false;
+    unsigned long long steps = 0;
+    int64_t launches = 0;
+    const int64_t bound = window_launch_bound();
+    int64_t tail_steps0 = 0;
+    while (n > 0) {
+        const bool tail = n < tu.tail && (peak >= tu.tail || !grew);
+        if (tail && !in_tail) {
+            in_tail = true;
+            tail_steps0 = (int64_t)steps;
+        }
+        const bool bulk = n >= tu.tail;
+        const bool helper = !bulk && n_vac == n && n_gamma == 0 && n <= (uint32_t)kVacHelperBlock;
+        int K = 1;
+        HIPCHK(hipEventRecord(L.ev0, s));
+        if (bulk) {
+            rc = ensure_bulk_graph<P>(tu);
+            if (rc) return rc;
+            HIPCHK(hipGraphLaunch(L.gexec, s));
+            K = tu.K;
+        } else {
+            if (helper) launch_pool_helper<P>(0, s);
+            const int grid = (int)std::min<uint32_t>((n + kPoolWaves - 1) / kPoolWaves, (uint32_t)grid_full);
+            launch_pool<P>(0, grid, s);
+            launch_pool<P>(1, std::min(16 * grid, grid_full), s);
+            K = 2;
+            HIPCHK(hipGetLastError());
+        }
+        HIPCHK(hipEventRecord(L.ev1, s));
+        if (bulk) {
+            rc = read_ctrl();
+            if (rc) return rc;
+            unsigned long long c3[3];
+            HIPCHK(hipMemcpyAsync(c3, L.counters.p + kCSteps, sizeof(c3), hipMemcpyDeviceToHost, s));
+            HIPCHK(hipStreamSynchronize(s));
+            CtrlMirror& m = *L.h_mirror;
+            for (int t = 0; t < 3; ++t) m.count[t] = L.h_ctrl->count[0][t];
+            m.n_vac = 0;
+            m.overflow = L.h_ctrl->overflow;
+            m.steps = c3[0] + c3[1] + c3[2];
+        } else {
+            HIPCHK(hipStreamSynchronize(s));
+        }
+        const CtrlMirror m = *L.h_mirror;
+        float ms = 0.f;
+        HIPCHK(hipEventElapsedTime(&ms, L.ev0, L.ev1));
+        L.stats.kernel_ms += ms;
+        if (tail) L.stats.tail_kernel_ms += ms;
+        L.stats.kernel_launches += K;
+        L.stats.iterations += K;
+        L.stats.graph_replays += bulk ? 1 : 0;
+        launches += K;
+        if (m.overflow & 2u) return fail(GV_E_STATE, "compaction look-back wait exceeded its bound");
+        if (m.overflow) return GV_E_CAPACITY;
+        if (L.progress)
+            std::fprintf(stderr, "[gv] %s%s%s: %.3f ms, population %u/%u/%u, vacuum %u, steps %llu\n",
+                         bulk ? "bulk" : "pool", helper ? " helper" : "", tail ? " tail" : "", ms, m.count[0], m.count[1],
+                         m.count[2], m.n_vac, m.steps - steps);
+        steps = m.steps;
+        n_gamma = m.count[0];
+        n_vac = m.n_vac;
+        grew = m.count[0] + m.count[1] + m.count[2] > n;
+        n = m.count[0] + m.count[1] + m.count[2];
+        peak = std::max(peak, n);
+        if (launches > bound) return fail(GV_E_STATE, "step loop did not terminate within its launch bound");
+    }
+    if (in_tail) L.stats.tail_steps += (int64_t)steps - tail_steps0;
     return GV_OK;
 }
 
@@ -1065,7 +1228,8 @@ template <class P> int tuned_choice(int64_t n_events, uint64_t seed, std::array<
         if (rc) return rc;
         L.stats.iterations = 0;
         const double k0 = L.stats.kernel_ms;
-        rc = run_batched_window<P>(L.ev_start[0], L.ev_start[ne], tseed, tu);
+        rc = pool_mode() ? run_pool_window<P>(L.ev_start[0], L.ev_start[ne], tseed, tu)
+                         : run_batched_window<P>(L.ev_start[0], L.ev_start[ne], tseed, tu);
         if (rc == GV_E_CAPACITY) {
             rate = 0.0;
             return GV_OK;
@@ -1154,7 +1318,8 @@ template <class P> int transport_batched(int64_t n_events, uint64_t seed)
         const int64_t e1 = std::min(n_events, e0 + window);
         rc = snapshot_sinks();
         if (rc) return rc;
-        rc = run_batched_window<P>(ev_start[e0], ev_start[e1], seed, tu);
+        rc = pool_mode() ? run_pool_window<P>(ev_start[e0], ev_start[e1], seed, tu)
+                         : run_batched_window<P>(ev_start[e0], ev_start[e1], seed, tu);
         if (rc == GV_E_CAPACITY) {
             if (e1 - e0 <= 1) return fail(GV_E_CAPACITY, "track queues overflow with one event in flight");
             // undo the window's partial deposits, ledger rows and counters and
@@ -1340,6 +1505,9 @@ int gv_init(const gv_material* mats, int32_t n_mats, const gv_geometry* geom, co
     hipDeviceProp_t prop;
     HIPCHK(hipGetDeviceProperties(&prop, L.device));
     L.n_cu = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
+    int khz = 0;
+    HIPCHK(hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, L.device));
+    L.wall_khz = khz > 0 ? khz : 100000;
     HIPCHK(hipStreamCreateWithFlags(&L.own_stream, hipStreamNonBlocking));
     L.geom = g;
     L.phys = ph;
