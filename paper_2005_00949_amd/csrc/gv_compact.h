@@ -165,4 +165,171 @@ __device__ __forceinline__ void reserve3(uint32_t* count_out, uint32_t cap, cons
     __syncthreads();
 }
 
+// ---------------------------------------------------------------------------
+// The same compaction of codes already in memory (gv_compact3_noalloc), in two
+// launches: each block counts its inputs' codes per queue, then each block adds
+// up the totals of the blocks before it and places its own.  Codes are read
+// twice, but nothing waits: the single-pass look-back is for callers whose
+// counts are expensive to form again (the step kernel), and took 475 us for the
+// same million (3,907 chunks of 256 in one chain of look-backs).
+// One million inputs take 10.6 us this way, most of it the two launches; millions
+// of them are bound by HBM.
+// A thread takes ITEMS inputs in a row (16 from 2^20 inputs on: 48 bytes, three
+// 16-byte loads, and few enough blocks that adding up their totals is cheap;
+// 4 below, so that 100,000 inputs still fill the chip) and the block's outputs
+// go through LDS, so that each queue's run is written in order.
+// ---------------------------------------------------------------------------
+constexpr int kPartBlock = 256;
+constexpr unsigned long long kPartBad = 1ull << 48;   // beside three 16-bit counts: a code outside [-1, 2]
+
+// the codes of ITEMS inputs, four to a word; inputs past n read as -1
+template <int ITEMS, bool ALIGNED>
+__device__ __forceinline__ void part_load(const int8_t* codes, long long i0, long long n, uint32_t w[3 * ITEMS / 4])
+{
+    constexpr int W = 3 * ITEMS / 4;
+    if (ALIGNED && i0 + ITEMS <= n) {
+        if constexpr (ITEMS == 16) {
+            const uint4* p = reinterpret_cast<const uint4*>(codes + 3 * i0);
+#pragma unroll
+            for (int k = 0; k < W / 4; ++k) {
+                const uint4 v = p[k];
+                w[4 * k] = v.x;
+                w[4 * k + 1] = v.y;
+                w[4 * k + 2] = v.z;
+                w[4 * k + 3] = v.w;
+            }
+        } else {
+            const uint32_t* p = reinterpret_cast<const uint32_t*>(codes + 3 * i0);
+#pragma unroll
+            for (int k = 0; k < W; ++k) w[k] = p[k];
+        }
+        return;
+    }
+#pragma unroll
+    for (int k = 0; k < W; ++k) {
+        uint32_t v = 0;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            const long long at = 3 * i0 + 4 * k + b;
+            v |= (uint32_t)(uint8_t)(at < 3 * n ? codes[at] : (int8_t)-1) << (8 * b);
+        }
+        w[k] = v;
+    }
+}
+
+// codes per queue, 16 bits each (at most 3 * ITEMS * kPartBlock = 12,288 in a block)
+template <int W> __device__ __forceinline__ unsigned long long part_count(const uint32_t w[W], bool& bad)
+{
+    unsigned long long c = 0;
+#pragma unroll
+    for (int k = 0; k < 4 * W; ++k) {
+        const int q = (int)(int8_t)(w[k / 4] >> (8 * (k % 4)));
+        c += (q >= 0 && q <= 2) ? 1ull << (16 * (q & 3)) : 0ull;
+        bad |= q < -1 || q > 2;
+    }
+    return c;
+}
+
+template <int ITEMS, bool ALIGNED>
+__global__ void __launch_bounds__(kPartBlock) k_part_count(const int8_t* codes, long long n, unsigned long long* totals)
+{
+    __shared__ unsigned long long sum[kPartBlock / 64];
+    const long long i0 = ((long long)blockIdx.x * kPartBlock + threadIdx.x) * ITEMS;
+    uint32_t w[3 * ITEMS / 4];
+    part_load<ITEMS, ALIGNED>(codes, i0, n, w);
+    bool bad = false;
+    unsigned long long c = part_count<3 * ITEMS / 4>(w, bad);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off, 64);
+    if (__any(bad)) c |= kPartBad;
+    if ((threadIdx.x & 63) == 0) sum[threadIdx.x >> 6] = c;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        unsigned long long t = 0, f = 0;
+        for (int k = 0; k < kPartBlock / 64; ++k) {
+            t += sum[k] & (kPartBad - 1);
+            f |= sum[k] & kPartBad;
+        }
+        totals[blockIdx.x] = t | f;
+    }
+}
+
+template <int ITEMS, bool ALIGNED>
+__global__ void __launch_bounds__(kPartBlock) k_part_place(const int8_t* codes, long long n, int* index,
+                                                           uint32_t* counts, const unsigned long long* totals)
+{
+    constexpr int kWaves = kPartBlock / 64;
+    __shared__ unsigned long long wsum[kWaves];
+    __shared__ uint32_t before[kWaves][3];
+    __shared__ uint32_t flag;
+    __shared__ int out[3 * ITEMS * kPartBlock];
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const long long i0 = ((long long)blockIdx.x * kPartBlock + threadIdx.x) * ITEMS;
+    uint32_t w[3 * ITEMS / 4];
+    part_load<ITEMS, ALIGNED>(codes, i0, n, w);
+    bool bad = false;
+    const unsigned long long mine = part_count<3 * ITEMS / 4>(w, bad);
+    // inclusive scan of the wavefront's counts
+    unsigned long long inc = mine;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const unsigned long long v = __shfl_up(inc, off, 64);
+        inc += lane >= off ? v : 0ull;
+    }
+    if (threadIdx.x == 0) flag = 0;
+    if (lane == 63) wsum[wid] = inc;
+    // totals of the blocks before this one
+    uint32_t p[3] = {0, 0, 0};
+    bool any_bad = bad;
+    for (uint32_t j = threadIdx.x; j < blockIdx.x; j += kPartBlock) {
+        const unsigned long long t = totals[j];
+        p[0] += (uint32_t)t & 0xffffu;
+        p[1] += (uint32_t)(t >> 16) & 0xffffu;
+        p[2] += (uint32_t)(t >> 32) & 0xffffu;
+        any_bad |= (t & kPartBad) != 0;
+    }
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        const uint32_t v = wave_sum(p[q]);
+        if (lane == 0) before[wid][q] = v;
+    }
+    __syncthreads();
+    if (__any(any_bad) && lane == 0) atomicOr(&flag, 4u);
+    unsigned long long excl = inc - mine, tot = 0;
+    uint32_t base[3] = {0, 0, 0};
+#pragma unroll
+    for (int k = 0; k < kWaves; ++k) {
+        excl += k < wid ? wsum[k] : 0ull;
+        tot += wsum[k];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) base[q] += before[k][q];
+    }
+    const uint32_t t0 = (uint32_t)tot & 0xffffu, t1 = (uint32_t)(tot >> 16) & 0xffffu,
+                   t2 = (uint32_t)(tot >> 32) & 0xffffu;
+    // this block's outputs in LDS: queue 0's, then 1's, then 2's
+    uint32_t at[3] = {(uint32_t)excl & 0xffffu, t0 + ((uint32_t)(excl >> 16) & 0xffffu),
+                      t0 + t1 + ((uint32_t)(excl >> 32) & 0xffffu)};
+#pragma unroll
+    for (int k = 0; k < 3 * ITEMS; ++k) {
+        const int q = (int)(int8_t)(w[k / 4] >> (8 * (k % 4)));
+        const int v = (int)(i0 + k / 3) * 4 + k % 3;
+        if (q == 0) out[at[0]++] = v;
+        else if (q == 1) out[at[1]++] = v;
+        else if (q == 2) out[at[2]++] = v;
+    }
+    __syncthreads();
+    for (uint32_t k = threadIdx.x; k < t0 + t1 + t2; k += kPartBlock) {
+        const uint32_t q = k < t0 ? 0u : k < t0 + t1 ? 1u : 2u;
+        const uint32_t first = q == 0 ? 0u : q == 1 ? t0 : t0 + t1;
+        const uint32_t b = q == 0 ? base[0] : q == 1 ? base[1] : base[2];
+        index[(long long)q * 3 * n + b + (k - first)] = out[k];
+    }
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+        counts[0] = base[0] + t0;
+        counts[1] = base[1] + t1;
+        counts[2] = base[2] + t2;
+        counts[3] = flag;
+    }
+}
+
 }  // namespace gv
