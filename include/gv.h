@@ -275,7 +275,8 @@ typedef struct {
  *     tables from the same closed forms as any other implementation would,
  *     so no table blob crosses the boundary.
  * Binds the context to the current HIP device and replaces any previous
- * context (and its staged batch).  Nothing is retained from the caller.
+ * context (and its staged batch), whose device memory it uses again if that was
+ * on the same device.  Nothing is retained from the caller.
  * Errors: GV_E_INVALID_ARG (null pointer, count out of range, material
  * fractions), GV_E_GEOMETRY, GV_E_TABLES (grid, cuts, or a non-finite /
  * non-positive built value), GV_E_HIP, GV_E_STATE (called during a

@@ -282,38 +282,48 @@ template <int BLOCK> __device__ __forceinline__ void dep_flush(DepCache& dc, con
     __syncthreads();
 }
 
-// Final-state tables, one thread per (model, node): node energy, the density
+// Final-state tables: node energy, the density
 // of the transformed variable at kAlNX + 1 points, and Walker's alias table of
 // the sub-interval trapezoid weights (Vose's construction: scaled weights
 // below 1 and at or above 1 on two stacks filled in increasing index order; the
 // top small column keeps its share and hands the rest to the top large one).
-__global__ void k_build_alias(double* rec, int* alias, double* E, int* valid, double tc, double kc)
+// One wavefront per (model, energy) node: the densities are evaluated one per
+// lane (a lane working alone through all of them took 101 us, bound by its
+// chain of logs and divisions); the sum and the pairing, whose order the result
+// depends on, run on one lane out of LDS.
+__global__ void __launch_bounds__(64) k_build_alias(double* rec, int* alias, double* E, int* valid, double tc, double kc)
 {
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= kAlNMod * kAlNE) return;
+    __shared__ double pdf[kAlNX + 1], sc[kAlNX];
+    __shared__ int small[kAlNX], large[kAlNX];
+    __shared__ double total;
+    const int idx = blockIdx.x, lane = threadIdx.x;
     const int m = idx / kAlNE, j = idx % kAlNE;
     const double En = kAlE0 * pow(10.0, (double)j / kAlNPD);
-    if (m == 0) E[j] = En;
+    if (m == 0 && lane == 0) E[j] = En;
     double* r = rec + (size_t)idx * kAlRec;
     int* a = alias + (size_t)idx * kAlNX;
     const bool ok = alias_model_valid(m, En, tc, kc);
-    valid[idx] = ok ? 1 : 0;
+    if (lane == 0) valid[idx] = ok ? 1 : 0;
     if (!ok) {
-        for (int k = 0; k < kAlRec; ++k) r[k] = 0.0;
-        for (int k = 0; k < kAlNX; ++k) a[k] = k;
+        for (int k = lane; k < kAlRec; k += 64) r[k] = 0.0;
+        for (int k = lane; k < kAlNX; k += 64) a[k] = k;
         return;
     }
-    for (int k = 0; k <= kAlNX; ++k) r[k] = alias_pdf(m, En, (double)k / kAlNX, tc, kc);
-    double sc[kAlNX];
-    int small[kAlNX], large[kAlNX];
-    int ns = 0, nl = 0;
-    double sum = 0.0;
-    for (int k = 0; k < kAlNX; ++k) {
-        sc[k] = 0.5 * (r[k] + r[k + 1]);
-        sum += sc[k];
+    for (int k = lane; k <= kAlNX; k += 64) r[k] = pdf[k] = alias_pdf(m, En, (double)k / kAlNX, tc, kc);
+    __syncthreads();
+    for (int k = lane; k < kAlNX; k += 64) sc[k] = 0.5 * (pdf[k] + pdf[k + 1]);
+    __syncthreads();
+    if (lane == 0) {
+        double sum = 0.0;
+        for (int k = 0; k < kAlNX; ++k) sum += sc[k];
+        total = sum;
     }
+    __syncthreads();
+    for (int k = lane; k < kAlNX; k += 64) sc[k] = (double)kAlNX * sc[k] / total;
+    __syncthreads();
+    if (lane != 0) return;
+    int ns = 0, nl = 0;
     for (int k = 0; k < kAlNX; ++k) {
-        sc[k] = (double)kAlNX * sc[k] / sum;
         if (sc[k] < 1.0) small[ns++] = k;
         else large[nl++] = k;
     }
@@ -407,19 +417,27 @@ __global__ void k_build_range_bins(const double* E64, double* dR)
 }
 
 // running sum from R(E_0) = E_0 / S(E_0), in node order
-__global__ void k_build_range_scan(double* rec64, const double* E64, const double* dR)
+// One wavefront per (material, charge).  The sum runs node by node, in order,
+// over values the lanes hold, so that no addition waits for memory (one lane
+// reading a bin per addition took 119 us for 401 nodes).
+__global__ void __launch_bounds__(64) k_build_range_scan(double* rec64, const double* E64, const double* dR)
 {
-    const int n = c_phys.n_nodes;
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= 2 * c_phys.n_mats) return;
-    const int m = idx / 2, pos = idx & 1;
+    const int n = c_phys.n_nodes, lane = threadIdx.x;
+    const int m = blockIdx.x / 2, pos = blockIdx.x & 1;
     double* base = rec64 + (size_t)(m * 3 + (pos ? kPositron : kElectron)) * n * kCols;
     const double* d = dR + (size_t)(m * 2 + pos) * (n - 1);
     double R = E64[0] / dedx_total(c_phys.mat[m], E64[0], pos != 0, c_phys.t_cut, c_phys.k_cut);
-    base[3] = R;
-    for (int i = 0; i + 1 < n; ++i) {
-        R = R + d[i];
-        base[(i + 1) * kCols + 3] = R;
+    if (lane == 0) base[3] = R;
+    for (int i0 = 0; i0 + 1 < n; i0 += 64) {
+        const int i = i0 + lane;
+        const double di = i + 1 < n ? d[i] : 0.0;
+        double at = 0.0;
+#pragma unroll 16
+        for (int k = 0; k < 64; ++k) {
+            R = R + __shfl(di, k, 64);
+            at = lane == k ? R : at;
+        }
+        if (i + 1 < n) base[(i + 1) * kCols + 3] = at;
     }
 }
 

@@ -71,13 +71,14 @@ template <class T> struct DBuf {
         p = nullptr;
         n = 0;
     }
+    size_t bytes() const { return n * sizeof(T); }
 };
 
 // one set of SoA arrays: 3 types x 2 parities, `cap` slots each
 template <class P> struct QueueMem {
     using R = typename P::R;
     void* block = nullptr;
-    size_t cap = 0;
+    size_t cap = 0, bytes = 0;
     bool with_type = false;
     Soa<P> q[2][3];
     hipError_t alloc(size_t c, int n_sets, bool type_col)
@@ -91,6 +92,7 @@ template <class P> struct QueueMem {
             return e;
         }
         cap = c;
+        bytes = per * (size_t)n_sets;
         with_type = type_col;
         char* b = (char*)block;
         auto take = [&](size_t bytes) {
@@ -119,7 +121,7 @@ template <class P> struct QueueMem {
     {
         if (block) (void)hipFree(block);
         block = nullptr;
-        cap = 0;
+        cap = bytes = 0;
     }
 };
 
@@ -159,6 +161,8 @@ struct Lib {
     DBuf<float> al_rec32, al_E32;
     DBuf<int> al_alias, al_valid;
     DBuf<float> rec32, E32;
+    DBuf<double> bins, cut64;   // their build: range per bin, range at the tracking cut
+    DBuf<float> cut32;
     // transport state
     QueueMem<P64> q64;
     QueueMem<PMix> qmix;
@@ -205,6 +209,7 @@ struct Lib {
     double e_in = 0.0;
     int64_t tracks0[3] = {0, 0, 0};
     bool staged = false;
+    bool kept = false;   // device memory of a previous context is still here
     size_t staged_b = 0, staged_e = 0;   // window whose queue slots are on the device
     bool staged_one_queue = false;       // ... laid out for one mixed pool (plain) or per type
     // autotuner choices, per (precision, queue order, log2 of the batch size);
@@ -260,6 +265,38 @@ void drop_graph()
     L.gkey = GraphKey{};
 }
 
+// track queues, integration queue and the plain driver's arrays: all but a few
+// MB of what a context holds for events of ordinary number
+void release_queues()
+{
+    drop_graph();
+    L.q64.release();
+    L.qmix.release();
+    L.plain_pool.release();
+    L.pl_L.release();
+    L.pl_G.release();
+    L.pl_pr.release();
+    L.pl_o.release();
+    L.pl_active.release();
+    L.pl_stopped.release();
+    L.pl_nstep.release();
+    L.pl_volpre.release();
+    L.rk_jobs.release();
+    L.rk_jcap = 0;
+}
+
+// ensure(), and once more without the queues if the device has no room beside
+// them: they may be another context's, larger than this one needs (the
+// transport makes them again).  Not for buffers made after the queues.
+template <class T> hipError_t ensure_before_queues(DBuf<T>& b, size_t count)
+{
+    hipError_t e = b.ensure(count);
+    if (e != hipErrorOutOfMemory) return e;
+    (void)hipGetLastError();
+    release_queues();
+    return b.ensure(count);
+}
+
 void release_all()
 {
     drop_graph();
@@ -273,17 +310,10 @@ void release_all()
     L.al_E32.release();
     L.al_alias.release();
     L.al_valid.release();
-    L.q64.release();
-    L.qmix.release();
-    L.plain_pool.release();
-    L.pl_L.release();
-    L.pl_G.release();
-    L.pl_pr.release();
-    L.pl_o.release();
-    L.pl_active.release();
-    L.pl_stopped.release();
-    L.pl_nstep.release();
-    L.pl_volpre.release();
+    L.bins.release();
+    L.cut64.release();
+    L.cut32.release();
+    release_queues();
     L.ctrl.release();
     L.status.release();
     L.counters.release();
@@ -293,8 +323,6 @@ void release_all()
     L.esc_hist.release();
     L.trace_n.release();
     L.snap.release();
-    L.rk_jobs.release();
-    L.rk_jcap = 0;
     L.prim.release();
     L.prim_slot.release();
     if (L.h_ctrl) (void)hipHostFree(L.h_ctrl);
@@ -306,10 +334,37 @@ void release_all()
     L.ev0 = L.ev1 = nullptr;
     if (L.own_stream) (void)hipStreamDestroy(L.own_stream);
     L.own_stream = nullptr;
+    L.staged = L.kept = false;
+    L.hp.clear();
+    L.ev_start.clear();
+    L.tune_cache.clear();
+    L.ready = false;
+}
+
+// What gv_init drops of a context on the same device: everything that depends
+// on the detector.  Device memory stays for the next context to use, up to
+// kKeepBytes, and gv_finalize gives it back: the track queues alone are 12 GB,
+// and allocating them anew made a detector of a scan (set-up and 500 primaries
+// through a plate) take 339 ms instead of 0.67 ms, most of it the driver clearing
+// memory given back before.
+constexpr size_t kKeepBytes = (size_t)36 << 30;   // an eighth of the device: a driver's default queues
+
+void reset_context()
+{
+    const size_t held = L.q64.bytes + L.qmix.bytes + L.rk_jobs.bytes() + L.plain_pool.bytes + L.pl_L.bytes() +
+                        L.pl_G.bytes() + L.pl_pr.bytes() + L.pl_o.bytes() + L.edep.bytes() + L.ledger.bytes() +
+                        L.trace.bytes() + L.prim.bytes();
+    if (held > kKeepBytes) {
+        release_all();
+        return;
+    }
+    drop_graph();
+    L.esc_hist.release();   // gv_escape_hist reads zeros until the next transport
     L.staged = false;
     L.hp.clear();
     L.ev_start.clear();
     L.tune_cache.clear();
+    L.kept = true;
     L.ready = false;
 }
 
@@ -363,10 +418,9 @@ int build_tables()
     HIPCHK(L.rec32.ensure(nrec));
     HIPCHK(L.E64.ensure(n));
     HIPCHK(L.E32.ensure(n));
-    DBuf<double> dR;
+    DBuf<double>&dR = L.bins, &rt64 = L.cut64;
+    DBuf<float>& rt32 = L.cut32;
     HIPCHK(dR.ensure((size_t)nm * 2 * (n - 1)));
-    DBuf<double> rt64;
-    DBuf<float> rt32;
     HIPCHK(rt64.ensure(2 * nm));
     HIPCHK(rt32.ensure(2 * nm));
     hipStream_t s = stream();
@@ -375,7 +429,7 @@ int build_tables()
     HIPCHK(hipGetLastError());
     k_build_range_bins<<<(2 * (n - 1) * nm + 127) / 128, 128, 0, s>>>(L.E64.p, dR.p);
     HIPCHK(hipGetLastError());
-    k_build_range_scan<<<1, 64, 0, s>>>(L.rec64.p, L.E64.p, dR.p);
+    k_build_range_scan<<<2 * nm, 64, 0, s>>>(L.rec64.p, L.E64.p, dR.p);
     HIPCHK(hipGetLastError());
     k_to_float<<<(unsigned)((nrec + 255) / 256), 256, 0, s>>>(L.rec64.p, L.rec32.p, nrec);
     HIPCHK(hipGetLastError());
@@ -387,9 +441,6 @@ int build_tables()
     HIPCHK(hipMemcpyAsync(hr64.data(), rt64.p, 2 * nm * sizeof(double), hipMemcpyDeviceToHost, s));
     HIPCHK(hipMemcpyAsync(hr32.data(), rt32.p, 2 * nm * sizeof(float), hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
-    dR.release();
-    rt64.release();
-    rt32.release();
     for (size_t i = 0; i < nrec; ++i)
         if (!std::isfinite(h[i])) return fail(GV_E_TABLES, "non-finite table value");
     for (int m = 0; m < nm; ++m)
@@ -411,7 +462,7 @@ int build_tables()
     HIPCHK(L.al_E32.ensure(kAlNE));
     HIPCHK(L.al_alias.ensure((size_t)kAlNMod * kAlNE * kAlNX));
     HIPCHK(L.al_valid.ensure((size_t)kAlNMod * kAlNE));
-    k_build_alias<<<(kAlNMod * kAlNE + 63) / 64, 64, 0, s>>>(L.al_rec64.p, L.al_alias.p, L.al_E64.p, L.al_valid.p,
+    k_build_alias<<<kAlNMod * kAlNE, 64, 0, s>>>(L.al_rec64.p, L.al_alias.p, L.al_E64.p, L.al_valid.p,
                                                              L.phys.t_cut, L.phys.k_cut);
     HIPCHK(hipGetLastError());
     k_to_float<<<(unsigned)((arec + 255) / 256), 256, 0, s>>>(L.al_rec64.p, L.al_rec32.p, arec);
@@ -524,15 +575,15 @@ int ensure_common(int64_t n_events)
     const size_t ne = (size_t)n_events * (size_t)std::max(L.n_cells, 1);
     if (L.edep.n < ne) {
         drop_graph();
-        HIPCHK(L.edep.ensure(ne));
+        HIPCHK(ensure_before_queues(L.edep, ne));
     }
     if (L.ledger.n < (size_t)n_events * 4) {
         drop_graph();
-        HIPCHK(L.ledger.ensure((size_t)n_events * 4));
+        HIPCHK(ensure_before_queues(L.ledger, (size_t)n_events * 4));
     }
     if (L.cfg.trace_cap > 0 && L.trace.n < (size_t)L.cfg.trace_cap) {
         drop_graph();
-        HIPCHK(L.trace.ensure((size_t)L.cfg.trace_cap));
+        HIPCHK(ensure_before_queues(L.trace, (size_t)L.cfg.trace_cap));
     }
     HIPCHK(L.trace_n.ensure(1));
     if (!L.esc_hist.p) {
@@ -1159,6 +1210,8 @@ int ensure_plain_buffers(size_t cap)
 {
     if (L.plain_pool.cap != cap) {
         drop_graph();
+        if (L.kept) release_queues();   // another context's track queues
+        L.kept = false;
         HIPCHK(L.plain_pool.alloc(cap, 2, true));
         // the pool's parity-p queue lives at q[p][0]: remap the set layout
         QueueMem<P64>& Q = L.plain_pool;
@@ -1295,6 +1348,8 @@ template <class P> int transport_batched(int64_t n_events, uint64_t seed)
         // only one precision's queues are resident at a time
         L.q64.release();
         L.qmix.release();
+        if (L.kept) release_queues();   // another context's plain driver or integration queue
+        L.kept = false;
         HIPCHK(Q.alloc(cap, 6, false));
     }
     if (rk_queue_mode()) {
@@ -1500,16 +1555,20 @@ int gv_init(const gv_material* mats, int32_t n_mats, const gv_geometry* geom, co
         if (rc) return rc;
     }
     // ---- device ----
-    release_all();
+    int device = -1;
+    HIPCHK(hipGetDevice(&device));
+    if (L.own_stream && L.device == device) reset_context();
+    else release_all();
     L.cfg = default_config();
-    HIPCHK(hipGetDevice(&L.device));
-    hipDeviceProp_t prop;
-    HIPCHK(hipGetDeviceProperties(&prop, L.device));
-    L.n_cu = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
-    int khz = 0;
-    HIPCHK(hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, L.device));
-    L.wall_khz = khz > 0 ? khz : 100000;
-    HIPCHK(hipStreamCreateWithFlags(&L.own_stream, hipStreamNonBlocking));
+    if (!L.own_stream) {
+        int ncu = 0, khz = 0;
+        HIPCHK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, device));
+        HIPCHK(hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, device));
+        L.device = device;
+        L.n_cu = ncu > 0 ? ncu : 256;
+        L.wall_khz = khz > 0 ? khz : 100000;
+        HIPCHK(hipStreamCreateWithFlags(&L.own_stream, hipStreamNonBlocking));
+    }
     L.geom = g;
     L.phys = ph;
     L.n_cells = n_cells;
@@ -1600,7 +1659,7 @@ int gv_stage(const gv_primary* primaries, int64_t n)
     }
     L.n_events = n_events;
     L.n_prim = n;
-    HIPCHK(L.prim.ensure((size_t)n));
+    HIPCHK(ensure_before_queues(L.prim, (size_t)n));
     HIPCHK(hipMemcpyAsync(L.prim.p, L.hp.data(), (size_t)n * sizeof(PrimDev), hipMemcpyHostToDevice, stream()));
     HIPCHK(hipStreamSynchronize(stream()));
     L.staged_b = L.staged_e = (size_t)-1;
