@@ -21,9 +21,44 @@ namespace gv {
 enum : int { kMapUniform = 0, kMapSolenoid = 1 };
 enum : int { kFieldHelix = 0, kFieldRk4 = 1, kFieldRk45 = 2 };
 
+// sqrt(x) for x in [2^-700, 2^1000] and n / d for |d| in [2^-500, 2^500], |n|
+// below 2^500 (and above 2^-500 or so small that n / d counts for nothing): the
+// sequences the compiler expands sqrt and division into, which are correct to
+// the last bit, less the scaling that only numbers outside these ranges need.
+// root: Newton-Goldschmidt iteration of the reciprocal root with residual
+// corrections.  recip: two Newton steps; quot: one residual correction.
+__device__ __forceinline__ double root(double x)
+{
+#pragma clang fp contract(off)
+    const double y = __builtin_amdgcn_rsq(x);
+    double s = x * y, h = 0.5 * y;
+    const double e = fma(-h, s, 0.5);
+    s = fma(s, e, s);
+    h = fma(h, e, h);
+    s = fma(fma(-s, s, x), h, s);
+    return fma(fma(-s, s, x), h, s);
+}
+__device__ __forceinline__ bool root_ok(double x) { return (x >= 0x1p-700) & (x <= 0x1p1000); }
+__device__ __forceinline__ double recip(double d)
+{
+#pragma clang fp contract(off)
+    double r = __builtin_amdgcn_rcp(d);
+    r = fma(r, fma(-d, r, 1.0), r);
+    return fma(r, fma(-d, r, 1.0), r);
+}
+__device__ __forceinline__ double quot(double n, double d, double r)   // r = recip(d)
+{
+#pragma clang fp contract(off)
+    const double q = n * r;
+    return fma(fma(-d, q, n), r, q);
+}
+
 // Field at a point, in precision R.  sol_c = B0 / f(0) and sol_R2 = R^2 are
 // formed once on the host.
-template <class R> __device__ __forceinline__ void field_at(const DevGeom& g, const double x[3], R B[3])
+// NEAR (double): the caller has checked that coil and point are of ordinary size
+// (field_near), so roots and the division need no scaling.
+template <class R, bool NEAR = false>
+__device__ __forceinline__ void field_at(const DevGeom& g, const double x[3], R B[3])
 {
 #pragma clang fp contract(off)
     if (g.field_map != kMapSolenoid) {
@@ -35,9 +70,17 @@ template <class R> __device__ __forceinline__ void field_at(const DevGeom& g, co
     const R R2 = (R)g.sol_R2, L = (R)g.sol_L, c = (R)g.sol_c;
     const R z = (R)x[2];
     const R a = z + L, b = z - L;
-    const R sa = m_sqrt(R2 + a * a), sb = m_sqrt(R2 + b * b);
     // 1/sqrt(R^2 + a^2) and 1/sqrt(R^2 + b^2) from one division
-    const R r = (R)1 / (sa * sb);
+    R sa, sb, r;
+    if constexpr (NEAR) {
+        sa = root(R2 + a * a);
+        sb = root(R2 + b * b);
+        r = quot(1.0, sa * sb, recip(sa * sb));
+    } else {
+        sa = m_sqrt(R2 + a * a);
+        sb = m_sqrt(R2 + b * b);
+        r = (R)1 / (sa * sb);
+    }
     const R ia = sb * r, ib = sa * r;
     const R ia2 = ia * ia, ib2 = ib * ib;
     const R ia3 = ia2 * ia, ib3 = ib2 * ib;
@@ -49,6 +92,13 @@ template <class R> __device__ __forceinline__ void field_at(const DevGeom& g, co
     B[0] = (R)-0.5 * px * g1;
     B[1] = (R)-0.5 * py * g1;
     B[2] = g0 - (R)0.25 * r2 * g2;
+}
+
+// field_at<double, true> holds for |z| <= zmax
+__device__ __forceinline__ bool field_near(const DevGeom& g, double zmax)
+{
+    return g.field_map != kMapSolenoid ||
+           ((g.sol_R2 >= 0x1p-400) & (g.sol_R2 <= 0x1p400) & (g.sol_L <= 0x1p200) & (zmax <= 0x1p200));
 }
 
 template <class R> __device__ __forceinline__ void lorentz(R kq, const R B[3], const R u[3], R out[3])
@@ -162,38 +212,55 @@ struct Rk45State {
     bool busy;
 };
 
-__device__ inline void rk45_begin(const DevGeom& g, int type, double T, double s, double tol, const double pos[3],
-                                  const double u[3], Rk45State& st)
+// kq = q kKB / p, B0 the field at pos, theta the first attempt's turning angle
+__device__ __forceinline__ void rk45_start(double kq, const double B0[3], double theta, double s, const double pos[3],
+                                           const double u[3], Rk45State& st)
 {
 #pragma clang fp contract(off)
     st.acc = 0;
     st.rej = 0;
     st.done = 0.0;
     st.s = s;
-    st.busy = s > 0.0;
+    st.busy = true;
+    st.kq = kq;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         st.x[a] = pos[a];
         st.u[a] = u[a];
     }
-    if (!st.busy) return;
+    lorentz<double>(kq, B0, st.u, st.ku0);
+    st.h = s;
+    const double w = sqrt(st.ku0[0] * st.ku0[0] + st.ku0[1] * st.ku0[1] + st.ku0[2] * st.ku0[2]);
+    if (st.h * w > theta) st.h = theta / w;
+}
+__device__ __forceinline__ double rk45_theta(double tol) { return 0.8 * sqrt(sqrt(tol / kDpK)); }
+
+__device__ inline void rk45_begin(const DevGeom& g, int type, double T, double s, double tol, const double pos[3],
+                                  const double u[3], Rk45State& st)
+{
+#pragma clang fp contract(off)
+    if (!(s > 0.0)) {
+        st.acc = 0;
+        st.rej = 0;
+        st.done = 0.0;
+        st.s = s;
+        st.busy = false;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            st.x[a] = pos[a];
+            st.u[a] = u[a];
+        }
+        return;
+    }
     const double q = type == kElectron ? -1.0 : 1.0;
     const double p = sqrt(T * (T + 2.0 * kMe));
-    st.kq = q * kKB / p;
-    {
-        double B[3];
-        field_at<double>(g, st.x, B);
-        lorentz<double>(st.kq, B, st.u, st.ku0);
-    }
-    st.h = s;
-    {
-        const double w = sqrt(st.ku0[0] * st.ku0[0] + st.ku0[1] * st.ku0[1] + st.ku0[2] * st.ku0[2]);
-        const double theta = 0.8 * sqrt(sqrt(tol / kDpK));
-        if (st.h * w > theta) st.h = theta / w;
-    }
+    double B[3];
+    field_at<double>(g, pos, B);
+    rk45_start(q * kKB / p, B, rk45_theta(tol), s, pos, u, st);
 }
 
 // one attempt of a busy integration; clears busy when it is done
+template <bool NEAR = false>
 __device__ inline void rk45_attempt(const DevGeom& g, double tol, int max_sub, Rk45State& st)
 {
 #pragma clang fp contract(off)
@@ -224,7 +291,7 @@ __device__ inline void rk45_attempt(const DevGeom& g, double tol, int max_sub, R
             us[a] = fma(h, su, st.u[a]);
         }
         double B[3];
-        field_at<double>(g, xs, B);
+        field_at<double, NEAR>(g, xs, B);
 #pragma unroll
         for (int a = 0; a < 3; ++a) kx[i][a] = us[a];
         lorentz<double>(st.kq, B, us, ku[i]);

@@ -1120,33 +1120,63 @@ k_step_batched(BatchArgs<P> A)
     finish_launch(A.ctrl, pin, participants);
 }
 
-// Low-population helper of the tail replays.  When every track left is a
-// charged track in a volume without material (the loopers that end a
-// transport), the serial chain of their vacuum steps runs here, in a kernel
-// of few registers and without the step kernel's per-launch bookkeeping (a
-// lone looper in c4: ~0.95 us per step here, ~1.3 us inside the step
-// kernel), before the step kernel sees them.  A step is kept only if its track
-// stays alive in vacuum, which changes nothing but the track; the first step
-// that would end otherwise is left in the queue and taken by the step kernel
-// from the same state with the same arithmetic, so histories, deposits and
-// counters are the same as without the helper.  Any photon, track in
-// material or population above one workgroup makes it return at once.
+// Low-population helper.  When every track left is a charged track in a volume
+// without material (the loopers that end a transport), the serial chain of
+// their vacuum steps runs here, one wavefront per looper, so that each has a
+// SIMD to itself and none waits in another's divergent branch; each lane of it
+// steps the same track.  A step is kept only if its track stays alive in
+// vacuum, which changes nothing but the track; the first step that would end
+// otherwise is left in the queue and taken by the step kernel from the same
+// state with the same arithmetic, so histories, deposits and counters are the
+// same as without the helper.  Any photon, track in material or population
+// above one looper per wavefront makes it return at once.
 constexpr int kVacHelperBlock = 256;
+constexpr int kVacHelperWaves = kVacHelperBlock / 64;
 
 // The helper's step forms: the looper forms of the helix in a uniform field
-// (the world step and the vacuum step), the general step with the helix in a
-// field map, or the general step with the field integrators; each is the
-// function the step kernel runs for such a track.
+// (the world step, the vacuum step and runs of either), the helix in a field
+// map (the general step and runs in a shell), or the general step with the
+// field integrators; each takes the steps of the function the step kernel runs
+// for such a track.
 enum : int { kHelperLooper = 0, kHelperHelix = 1, kHelperInteg = 2 };
 
-// tracer: the lane that writes the step records (in the one-wavefront-per-
-// looper form every lane steps the same track, and lane 0 records it)
+// tracer: the lane that writes the step records (every lane steps the same
+// track, and lane 0 records it)
 template <class P, bool TRACE, int HM, class R = typename P::R>
-__device__ __forceinline__ void helper_steps(const BatchArgs<P>& A, const Ctx<P>& c, const WorldRun<P>& run,
-                                             Track<P>& t, int max_steps, int& calls, int& kept, RkSum& rks,
-                                             bool tracer)
+__device__ __forceinline__ void helper_steps(const BatchArgs<P>& A, const Ctx<P>& c, Track<P>& t, int max_steps,
+                                             int& calls, int& kept, RkSum& rks, bool tracer)
 {
-    for (; calls < max_steps;) {
+    // vacuum keeps the kinetic energy: the run constants hold for every kept step
+    const WorldRun<P> run = world_run(c, t);
+    FieldStep<P> f = field_step(c, t);
+    const int axis = field_axis(f);
+    const bool slabs = c_geom.axis == 0, rk45 = c_phys.field_method == kFieldRk45;
+    for (;;) {
+        if constexpr (!TRACE) {
+            int m = 0;
+            RkTally rk{0, 0, 0};
+            if constexpr (HM == kHelperInteg) {
+                if (rk45) m = run_shell<P, kRunRk45>(c, f, t, max_steps - calls, rk);
+                rks.acc += (uint32_t)rk.acc;
+                rks.rej += (uint32_t)rk.rej;
+                rks.slots += (uint32_t)rk.iters;
+            } else if constexpr (HM == kHelperHelix) {
+                m = run_shell<P, kRunMap>(c, f, t, max_steps - calls, rk);
+            } else if (slabs) {
+                const int left = max_steps - calls;
+                if (axis == 0) m = run_world<P, 0>(c, run, f, t, left);
+                else if (axis == 1) m = run_world<P, 1>(c, run, f, t, left);
+                else if (axis == 2) m = run_world<P, 2>(c, run, f, t, left);
+                else m = run_world<P, -1>(c, run, f, t, left);
+            } else if (axis == 2) {
+                m = run_shell<P, kRunHelix, 2>(c, f, t, max_steps - calls, rk);
+            } else {
+                m = run_shell<P, kRunHelix>(c, f, t, max_steps - calls, rk);
+            }
+            calls += m;
+            kept += m;
+        }
+        if (calls >= max_steps) break;
         Track<P> tn = t;
         StepOut<R> o;
         const uint32_t ns = t.nstep;
@@ -1185,68 +1215,40 @@ __global__ void __launch_bounds__(kVacHelperBlock) k_vacuum_helper(BatchArgs<P> 
     const uint32_t n0 = min(A.ctrl->count[pin][kGamma], A.cap);
     const uint32_t n1 = min(A.ctrl->count[pin][kElectron], A.cap);
     const uint32_t n2 = min(A.ctrl->count[pin][kPositron], A.cap);
-    if (n0 != 0 || n1 + n2 == 0 || n1 + n2 > (uint32_t)kVacHelperBlock) return;
-    const uint32_t i = threadIdx.x;
-    const bool active = i < n1 + n2;
-    const int ty = i < n1 ? kElectron : kPositron;
-    const uint32_t slot = i < n1 ? i : i - n1;
-    Track<P> t;
-    if (active) {
-        load_track(A.in[ty], slot, ty, t);
-        t.type = ty;
+    const uint32_t n = n1 + n2;
+    if (n0 != 0 || n == 0 || n > gridDim.x * (uint32_t)kVacHelperWaves) return;
+    // Every block looks at every track, so that all come to the same answer.  A
+    // block that has begun may already have written its tracks back: their
+    // volumes are still without material.
+    bool vac = true;
+    for (uint32_t i = threadIdx.x; i < n; i += kVacHelperBlock) {
+        const int v = i < n1 ? A.in[kElectron].vol[i] : A.in[kPositron].vol[i - n1];
+        vac = vac && v != kOutside && vol_material(c_geom, v) < 0;
     }
-    const bool vac = !active || (t.vol != kOutside && vol_material(c_geom, t.vol) < 0);
     if (!__syncthreads_and(vac)) return;
+    const uint32_t w = blockIdx.x * (uint32_t)kVacHelperWaves +
+                       (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    if (w >= n) return;
+    const int ty = w < n1 ? kElectron : kPositron;
+    const uint32_t slot = w < n1 ? w : w - n1;
     Ctx<P> c{A.ctrl->seed, &c_geom, &c_phys, A.tv};
+    Track<P> t;
+    load_track(A.in[ty], slot, ty, t);
     int calls = 0, kept = 0;
-    if (n1 + n2 <= (uint32_t)(kVacHelperBlock / 64)) {
-        // Few loopers (the usual end of a transport): one wavefront per
-        // looper, so that loopers step side by side on separate SIMDs
-        // instead of taking turns in the divergent branches of one wavefront
-        // (the arithmetic is the same).
-        const uint32_t w = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-        if (w >= n1 + n2) return;
-        const int tw = w < n1 ? kElectron : kPositron;
-        const uint32_t sw = w < n1 ? w : w - n1;
-        Track<P> tu;
-        load_track(A.in[tw], sw, tw, tu);
-        const WorldRun<P> run = world_run(c, tu);
-        RkSum rks{0u, 0u, 0u};
-        const bool lane0 = (threadIdx.x & 63) == 0;
-        if (A.S.trace) helper_steps<P, true, HM>(A, c, run, tu, max_steps, calls, kept, rks, lane0);
-        else helper_steps<P, false, HM>(A, c, run, tu, max_steps, calls, kept, rks, lane0);
-        if (lane0) {
-            // (one looper per wavefront: its integration counts once, as one lane's)
-            helper_rk_counts(A.S, rks);
-            if (kept) {
-                store_track(A.in[tw], sw, tu);
-                atomicAdd(&A.S.counters[kCSteps + tw], (unsigned long long)kept);
-                atomicAdd(&A.S.counters[kCHelperSteps], (unsigned long long)kept);
-            }
-            if (calls) atomicAdd(&A.S.counters[kCLaneSlots], 64ull * (unsigned)calls);
-        }
-        return;
-    }
-    if (active) {
-        // vacuum keeps the kinetic energy: the run constants hold for every
-        // kept step.  Without a trace the loop is its own copy, in which the
-        // step records' other fields are dead.
-        const WorldRun<P> run = world_run(c, t);
-        RkSum rks{0u, 0u, 0u};
-        if (A.S.trace) helper_steps<P, true, HM>(A, c, run, t, max_steps, calls, kept, rks, true);
-        else helper_steps<P, false, HM>(A, c, run, t, max_steps, calls, kept, rks, true);
+    RkSum rks{0u, 0u, 0u};
+    const bool lane0 = (threadIdx.x & 63) == 0;
+    if (A.S.trace) helper_steps<P, true, HM>(A, c, t, max_steps, calls, kept, rks, lane0);
+    else helper_steps<P, false, HM>(A, c, t, max_steps, calls, kept, rks, lane0);
+    if (lane0) {
+        // (one looper per wavefront: its integration counts once, as one lane's)
         helper_rk_counts(A.S, rks);
         if (kept) {
             store_track(A.in[ty], slot, t);
             atomicAdd(&A.S.counters[kCSteps + ty], (unsigned long long)kept);
             atomicAdd(&A.S.counters[kCHelperSteps], (unsigned long long)kept);
         }
+        if (calls) atomicAdd(&A.S.counters[kCLaneSlots], 64ull * (unsigned)calls);
     }
-    // lane slots: the wavefront ran as many step calls as its busiest lane
-    int m = calls;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) m = max(m, __shfl_xor(m, off, 64));
-    if ((threadIdx.x & 63) == 0 && m) atomicAdd(&A.S.counters[kCLaneSlots], 64ull * (unsigned)m);
 }
 
 // ===========================================================================

@@ -827,6 +827,9 @@ template <> QueueMem<PMix>& batch_queues<PMix>() { return L.qmix; }
 // for RK45 with arrival order, integration inside the step only
 // vacuum steps per track and helper launch in the tail replays
 constexpr int kVacHelperSteps = 4096;
+// its blocks there, for 256 loopers (most of its launches find material and leave;
+// the pool driver, which launches it only for loopers, gives it a block per CU)
+constexpr int kVacHelperGraphGrid = 64;
 
 template <class P>
 int capture(const Tuning& tu, int grid, int K, int inner_bulk, int inner_tail, bool tail, hipGraph_t* g,
@@ -866,11 +869,11 @@ int capture(const Tuning& tu, int grid, int K, int inner_bulk, int inner_tail, b
     for (int k = 0; k < K; ++k) {
         if (tail) {
             if (L.cfg.field_method != GV_FIELD_HELIX)
-                k_vacuum_helper<P, kHelperInteg><<<1, kVacHelperBlock, 0, s>>>(A[k & 1], kVacHelperSteps);
+                k_vacuum_helper<P, kHelperInteg><<<kVacHelperGraphGrid, kVacHelperBlock, 0, s>>>(A[k & 1], kVacHelperSteps);
             else if (L.geom.field_map == kMapUniform)
-                k_vacuum_helper<P, kHelperLooper><<<1, kVacHelperBlock, 0, s>>>(A[k & 1], kVacHelperSteps);
+                k_vacuum_helper<P, kHelperLooper><<<kVacHelperGraphGrid, kVacHelperBlock, 0, s>>>(A[k & 1], kVacHelperSteps);
             else
-                k_vacuum_helper<P, kHelperHelix><<<1, kVacHelperBlock, 0, s>>>(A[k & 1], kVacHelperSteps);
+                k_vacuum_helper<P, kHelperHelix><<<kVacHelperGraphGrid, kVacHelperBlock, 0, s>>>(A[k & 1], kVacHelperSteps);
         }
         if (rkq) launch_rk_queue_step<P>(tu.block, A[k & 1], grid, s, tail);
         else launch_step_dispatch<P>(tu.block, A[k & 1], grid, stable, s);
@@ -1017,7 +1020,7 @@ constexpr int kPoolBudget = 100;
 constexpr int kPoolInner = 8;
 constexpr int kPoolInnerInteg = 2;
 // vacuum steps per track and helper launch between two pool launches
-constexpr int kPoolHelperSteps = 16384;
+constexpr int kPoolHelperSteps = 65536;
 
 template <class P> void launch_pool(int parity, int grid, hipStream_t s)
 {
@@ -1050,11 +1053,11 @@ template <class P> void launch_pool_helper(int parity, hipStream_t s)
     A.S = make_sinks();
     A.tv = tab_view<typename P::R>();
     if (L.cfg.field_method != GV_FIELD_HELIX)
-        k_vacuum_helper<P, kHelperInteg><<<1, kVacHelperBlock, 0, s>>>(A, kVacHelperSteps);
+        k_vacuum_helper<P, kHelperInteg><<<L.n_cu, kVacHelperBlock, 0, s>>>(A, kVacHelperSteps);
     else if (L.geom.field_map == kMapUniform)
-        k_vacuum_helper<P, kHelperLooper><<<1, kVacHelperBlock, 0, s>>>(A, kPoolHelperSteps);
+        k_vacuum_helper<P, kHelperLooper><<<L.n_cu, kVacHelperBlock, 0, s>>>(A, kPoolHelperSteps);
     else
-        k_vacuum_helper<P, kHelperHelix><<<1, kVacHelperBlock, 0, s>>>(A, kPoolHelperSteps);
+        k_vacuum_helper<P, kHelperHelix><<<L.n_cu, kVacHelperBlock, 0, s>>>(A, kPoolHelperSteps);
 }
 
 // Batched transport of one event window with the pool kernel.  Populations
@@ -1085,7 +1088,7 @@ template <class P> int run_pool_window(size_t b, size_t e, uint64_t seed, const 
             tail_steps0 = (int64_t)steps;
         }
         const bool bulk = n >= tu.tail;
-        const bool helper = !bulk && n_vac == n && n_gamma == 0 && n <= (uint32_t)kVacHelperBlock;
+        const bool helper = !bulk && n_vac == n && n_gamma == 0 && n <= (uint32_t)(L.n_cu * kVacHelperWaves);
         int K = 1;
         HIPCHK(hipEventRecord(L.ev0, s));
         if (bulk) {

@@ -917,4 +917,359 @@ __device__ inline void step_world(const Ctx<P>& c, const WorldRun<P>& k, Track<P
     t.nstep += 1;
 }
 
+// ---- runs of vacuum steps -------------------------------------------------
+// A looper's steps in vacuum, one after another, for the kernel that does
+// nothing else (k_vacuum_helper).  A run takes steps as long as each stays in its
+// volume, keeps only what such a step changes (position, direction, step
+// count), and stops before the first step that may be any other; the caller
+// takes that one in its general form from the same state.  Where every boundary
+// certainly lies beyond the step, its distance is not formed; where it may not,
+// the general form's is (loopers that graze a wall).  Every value a step
+// stores comes from the expressions of step_track in their order, so the bits
+// are the same; what only decides between outcomes is tested by bounds with a
+// margin (2^-40 for products against distances, 2^-30 R^2 for squared radii, at
+// least 10^5 times the rounding of either side):
+//   * a plane lies beyond the step if the step's extent along its axis is
+//     shorter than the distance to it (slab_world, shell_exit: quotients);
+//   * the outer cylinder lies beyond the step if the step's straight end is
+//     inside it (the far root of cyl_out); the inner one if the straight line
+//     moves outward, ends outside it while still inward bound, or passes it by
+//     (cyl_in: no root, or the near root).
+// A lone looper is a serial chain on one SIMD, bound by the latency of each
+// instruction and most of all by its branches (nothing else is there to issue
+// meanwhile): so a step's move, the test of where it ended and the plan of the
+// next step are straight-line code with one branch (165 instructions in a shell
+// with the field along its axis).  Loopers of the barrel's gaps took 1.66 us per
+// step in general form and take 0.44 us this way, the grazing ones included.
+template <class P> struct FieldStep {
+    using R = typename P::R;
+    double p, q;      // momentum, charge sign
+    R pf, chord;      // momentum in the policy's precision, bending tolerance
+    R b[3], kBf;      // field direction and curvature constant (uniform field)
+    double kq;        // -(q kB / p)
+};
+
+template <class P, class R = typename P::R>
+__device__ __forceinline__ FieldStep<P> field_step(const Ctx<P>& c, const Track<P>& t)
+{
+#pragma clang fp contract(off)
+    FieldStep<P> f;
+    const DevGeom& g = *c.g;
+    const double Td = (double)t.T;
+    f.q = t.type == kElectron ? -1.0 : 1.0;
+    f.p = sqrt(Td * (Td + 2.0 * kMe));
+    f.pf = m_sqrt(t.T * (t.T + (R)(2.0 * kMe)));
+    f.chord = (R)c.ph->chord_tol;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) f.b[a] = (R)g.Bhat[a];
+    f.kBf = (R)g.kB;
+    f.kq = -(f.q * g.kB / f.p);
+    return f;
+}
+
+// AXIS: the field lies along that axis (of either sign); then two of the
+// products and half of the sums below multiply by or add zero and are left out,
+// which changes no bit but the sign of a zero.  AXIS < 0: any direction.
+// the bending estimate of stage_move (infinite where sin2 is 0)
+template <class P, int AXIS = -1, class R = typename P::R>
+__device__ __forceinline__ double bending(const FieldStep<P>& f, const R u[3])
+{
+#pragma clang fp contract(off)
+    R sin2;
+    if constexpr (AXIS >= 0) {
+        const R ua = u[(AXIS + 1) % 3], uc = u[(AXIS + 2) % 3];
+        sin2 = ua * ua + uc * uc;
+    } else {
+        const R cx = u[1] * f.b[2] - u[2] * f.b[1], cy = u[2] * f.b[0] - u[0] * f.b[2],
+                cz = u[0] * f.b[1] - u[1] * f.b[0];
+        sin2 = cx * cx + cy * cy + cz * cz;
+    }
+    const R rc = f.pf / (f.kBf * m_sqrt(sin2));
+    return (double)m_sqrt((R)2 * rc * f.chord);
+}
+
+// m_sin without its branch
+__device__ __forceinline__ double sin_flat(double x) { return sin(x); }
+__device__ __forceinline__ float sin_flat(float x)
+{
+    const float a = sin_small(x), b = __sinf(x);
+    return fabsf(x) <= kQuarterPi ? a : b;
+}
+
+constexpr double kSmallTurn = 1.0e-4;   // below it helix_move takes its series
+
+// helix_move over s with turning angle th = kq s; SMALL: |th| may lie below 1e-4
+template <class P, int AXIS, bool SMALL, class R = typename P::R>
+__device__ __forceinline__ void helix_step(const FieldStep<P>& f, double s, double th, const double x[3], const R u[3],
+                                           double y[3], R v[3])
+{
+#pragma clang fp contract(off)
+    const double thr = sizeof(R) == sizeof(double) ? th : th - 2.0 * kPi * rint(th * (0.5 / kPi));
+    const R sn = sin_flat((R)thr), hs = sin_flat((R)(0.5 * thr));
+    const R omc = (R)2 * hs * hs;
+    R f1 = sn / (R)th, f2 = omc / (R)th;
+    if (SMALL && fabs(th) < kSmallTurn) {
+        f1 = (R)(1.0 - th * th / 6.0);
+        f2 = (R)(0.5 * th);
+    }
+    const R cs = (R)1 - omc;
+    if constexpr (AXIS >= 0) {
+        constexpr int a = (AXIS + 1) % 3, c = (AXIS + 2) % 3;
+        const R g2 = f.b[AXIS] * f2, gn = f.b[AXIS] * sn;
+        y[a] = x[a] + s * (double)(f1 * u[a] - g2 * u[c]);
+        y[c] = x[c] + s * (double)(f1 * u[c] + g2 * u[a]);
+        y[AXIS] = x[AXIS] + s * (double)u[AXIS];
+        v[a] = cs * u[a] - gn * u[c];
+        v[c] = cs * u[c] + gn * u[a];
+        v[AXIS] = u[AXIS];
+    } else {
+        const R upar = u[0] * f.b[0] + u[1] * f.b[1] + u[2] * f.b[2];
+        const R up[3] = {u[0] - upar * f.b[0], u[1] - upar * f.b[1], u[2] - upar * f.b[2]};
+        const R bxu[3] = {f.b[1] * up[2] - f.b[2] * up[1], f.b[2] * up[0] - f.b[0] * up[2],
+                          f.b[0] * up[1] - f.b[1] * up[0]};
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            y[a] = x[a] + s * (double)(upar * f.b[a] + f1 * up[a] + f2 * bxu[a]);
+            v[a] = upar * f.b[a] + cs * up[a] + sn * bxu[a];
+        }
+    }
+    normalise(v);
+}
+// whether no step in a uniform field turns by less (a step is no shorter than
+// the bending estimate, which is least across the field)
+template <class P> __device__ __forceinline__ bool turns(const FieldStep<P>& f)
+{
+#pragma clang fp contract(off)
+    const double rho = (double)f.pf / (double)f.kBf;
+    return fabs(f.kq) * sqrt(2.0 * rho * (double)f.chord) > 1.01 * kSmallTurn;
+}
+
+// the axis a uniform field lies along, or -1
+template <class P> __device__ __forceinline__ int field_axis(const FieldStep<P>& f)
+{
+    const bool n0 = f.b[0] != 0, n1 = f.b[1] != 0, n2 = f.b[2] != 0;
+    return n0 ? (n1 | n2 ? -1 : 0) : n1 ? (n2 ? -1 : 1) : 2;
+}
+
+// the steps a run may take before the looper cap
+template <class P> __device__ __forceinline__ int run_bound(const Ctx<P>& c, const Track<P>& t, int n)
+{
+    const long long left = (long long)c.ph->max_steps - (long long)t.nstep;
+    return left < (long long)n ? (left > 0 ? (int)left : 0) : n;
+}
+
+// in the world volume of a slab stack, uniform field
+template <class P, int AXIS, class R = typename P::R>
+__device__ __forceinline__ int run_world(const Ctx<P>& c, const WorldRun<P>& k, const FieldStep<P>& f, Track<P>& t, int n)
+{
+#pragma clang fp contract(off)
+    if (!k.lean || t.vol != 0 || !turns(f)) return 0;
+    const DevGeom& g = *c.g;
+    n = run_bound(c, t, n);
+    const double e0 = g.env[0], e1 = g.env[1], w0 = g.world[0], w1 = g.world[1], w2 = g.world[2], w3 = g.world[3];
+    // the plan of a step from x along u: its length and turning angle; in:
+    // whether x lies in the world (locate); returns whether every boundary
+    // certainly lies beyond the step
+    auto plan = [&](const double x[3], const R u[3], double& s, double& th, bool& in) -> bool {
+        const double d[3] = {(double)u[0], (double)u[1], (double)u[2]};
+        // distances to the walls, and to the envelope along each axis
+        const double ax = w0 - fabs(x[0]), ay = w1 - fabs(x[1]), az = fmin(x[2] - w2, w3 - x[2]);
+        const double ex = fabs(x[0]) - e0, ey = fabs(x[1]) - e1, ez0 = k.zlo - x[2], ez1 = x[2] - k.zhi;
+        const double walls = fmin(fmin(ax, ay), az);
+        // slab_world_safety against the bending estimate
+        const double qx = fmax(ex, 0.0), qy = fmax(ey, 0.0), qz = fmax(fabs(x[2] - k.zc) - k.zh, 0.0);
+        const double qq = qx * qx + qy * qy + qz * qz;
+        in = (fmax(fmax(ex, ey), fmax(ez0, ez1)) > 0.0) & (walls >= 0.0) & root_ok(qq);
+        double sf = fmin(walls, root(qq));
+        sf = sf > 0.0 ? sf : 0.0;
+        s = fmax(bending<P, AXIS>(f, u), sf);
+        th = f.kq * s;
+        const double sm = s * (1.0 + 0x1p-40);
+        const double rx = sm * fabs(d[0]), ry = sm * fabs(d[1]), rz = sm * fabs(d[2]);
+        const bool exit_far = (ax > rx) & (ay > ry) & (az > rz);
+        // (moving away from the envelope along an axis, or not reaching it there)
+        const bool entry_far = ((ex > 0.0) & ((x[0] * d[0] >= 0.0) | (ex > rx))) |
+                               ((ey > 0.0) & ((x[1] * d[1] >= 0.0) | (ey > ry))) |
+                               ((ez0 > 0.0) & ((d[2] <= 0.0) | (ez0 > rz))) |
+                               ((ez1 > 0.0) & ((d[2] >= 0.0) | (ez1 > rz)));
+        return exit_far & entry_far;
+    };
+    double x[3] = {t.x[0], t.x[1], t.x[2]}, s, th;
+    R u[3] = {t.u[0], t.u[1], t.u[2]};
+    bool in;
+    bool far = plan(x, u, s, th, in);
+    if (n <= 0 || !in) return 0;
+    double y[3];
+    R v[3];
+    int i = 0;
+    for (;;) {
+        if (far) {
+            for (;;) {
+                helix_step<P, AXIS, false>(f, s, th, x, u, y, v);
+                far = plan(y, v, s, th, in);
+                ++i;
+                if (!(in & far & (i < n))) break;
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    x[a] = y[a];
+                    u[a] = v[a];
+                }
+            }
+        } else {
+            const double d[3] = {(double)u[0], (double)u[1], (double)u[2]};
+            const double db = slab_world(g, x, d).t;
+            if (db <= s) s = db + k.push;
+            th = f.kq * s;
+            helix_step<P, AXIS, true>(f, s, th, x, u, y, v);
+            far = plan(y, v, s, th, in);
+            ++i;
+        }
+        if (!in) break;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            x[a] = y[a];
+            u[a] = v[a];
+        }
+        if (i >= n) break;
+    }
+    i -= in ? 0 : 1;   // the last step left the world: not one of this run
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        t.x[a] = x[a];
+        t.u[a] = u[a];
+    }
+    t.nstep += (uint32_t)i;
+    return i;
+}
+
+// in a shell without material: helix in a uniform field, helix in the field map
+// (in the field at the step's start), or adaptive Runge-Kutta in either field
+enum : int { kRunHelix = 0, kRunMap = 1, kRunRk45 = 2 };
+
+template <class P, int MODE, int AXIS = -1, class R = typename P::R>
+__device__ __forceinline__ int run_shell(const Ctx<P>& c, FieldStep<P>& f, Track<P>& t, int n, RkTally& tally)
+{
+#pragma clang fp contract(off)
+    const DevGeom& g = *c.g;
+    tally.acc = tally.rej = tally.iters = 0;
+    const bool map = MODE == kRunMap || (MODE == kRunRk45 && g.field_map == kMapSolenoid);
+    if (g.axis != 1 || t.vol < 1 || t.type == kGamma || t.T < (R)c.ph->t_track || (!map && g.Bmag == 0.0)) return 0;
+    const double rin = g.bounds[t.vol - 1], rout = g.bounds[t.vol], H = g.env[0];
+    if (MODE == kRunHelix ? !turns(f) : !field_near(g, H)) return 0;
+    if (!(rout <= 0x1p400)) return 0;
+    n = run_bound(c, t, n);
+    const double margin = 0x1p-30 * (rout * rout);
+    // (the bore has no inner wall: any radius is beyond it)
+    const double in2 = rin > 0.0 ? rin * rin + margin : -kInf, out2 = rout * rout - margin;
+    const double wall = rin > 0.0 ? rin : -kInf;
+    const double rp = recip(f.p);
+    const double kq45 = f.q * kKB / f.p, theta = MODE == kRunRk45 ? rk45_theta(c.ph->rk_tol) : 0.0;
+    double B[3] = {g.B[0], g.B[1], g.B[2]};   // the field at x (of the next step)
+    auto plan = [&](const double x[3], const R u[3], double& s, double& th, bool& in) -> bool {
+        bool ok = true;
+        if (map) {
+            field_at<double, true>(g, x, B);
+            const double B2 = B[0] * B[0] + B[1] * B[1] + B[2] * B[2];
+            const double Bm = root(B2);
+            ok = (B2 >= 0x1p-400) & (B2 <= 0x1p400);
+            const double kB = kKB * Bm, rB = recip(Bm);
+#pragma unroll
+            for (int a = 0; a < 3; ++a) f.b[a] = (R)quot(B[a], Bm, rB);
+            f.kBf = (R)kB;
+            if constexpr (MODE == kRunMap) f.kq = -quot(f.q * kB, f.p, rp);
+        }
+        const double d[3] = {(double)u[0], (double)u[1], (double)u[2]};
+        const double az = H - fabs(x[2]);
+        const double r2 = x[0] * x[0] + x[1] * x[1];
+        const double r = root(r2);
+        in = (az >= 0.0) & (rin <= r) & (r < rout);   // locate: this shell (on the axis r is NaN: not)
+        // shell_safety against the bending estimate
+        double sf = fmin(fmin(rout - r, r - wall), az);
+        sf = sf > 0.0 ? sf : 0.0;
+        s = fmax(bending<P, AXIS>(f, u), sf);
+        th = f.kq * s;
+        const double a2 = d[0] * d[0] + d[1] * d[1];
+        const double bb = x[0] * d[0] + x[1] * d[1];
+        const double sa = s * a2;
+        const double end2 = r2 + s * (2.0 * bb + sa);   // squared radius of the straight end
+        in = in & ok;
+        return (end2 < out2) & (az > s * (1.0 + 0x1p-40) * fabs(d[2])) &
+               ((bb >= 0.0) | ((end2 > in2) & (bb + sa <= 0.0)) | (r2 * a2 - bb * bb > in2 * a2)) &
+               (MODE == kRunMap ? fabs(th) >= kSmallTurn : true);
+    };
+    double x[3] = {t.x[0], t.x[1], t.x[2]}, s, th;
+    R u[3] = {t.u[0], t.u[1], t.u[2]};
+    bool in;
+    bool far = plan(x, u, s, th, in);
+    if (n <= 0 || !in) return 0;
+    const double push = c.ph->push;
+    double y[3];
+    R v[3];
+    int i = 0, acc = 0, rej = 0;
+    auto integrate = [&]() {
+        Rk45State st;
+        const double d[3] = {(double)u[0], (double)u[1], (double)u[2]};
+        rk45_start(kq45, B, theta, s, x, d, st);
+        while (st.busy) rk45_attempt<true>(g, c.ph->rk_tol, c.ph->rk_max_sub, st);
+        normalise(st.u);
+        acc = st.acc;
+        rej = st.rej;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            y[a] = st.x[a];
+            v[a] = (R)st.u[a];
+        }
+    };
+    for (;;) {
+        if (far && MODE != kRunRk45) {
+            for (;;) {
+                helix_step<P, AXIS, false>(f, s, th, x, u, y, v);
+                far = plan(y, v, s, th, in);
+                ++i;
+                if (!(in & far & (i < n))) break;
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    x[a] = y[a];
+                    u[a] = v[a];
+                }
+            }
+        } else {
+            if (!far) {
+                const double d[3] = {(double)u[0], (double)u[1], (double)u[2]};
+                const double db = shell_exit(g, t.vol, x, d).t;
+                if (db <= s) s = db + push;
+            }
+            if (!(s > 0.0)) break;
+            if constexpr (MODE == kRunRk45) {
+                integrate();
+            } else {
+                th = f.kq * s;
+                helix_step<P, AXIS, true>(f, s, th, x, u, y, v);
+            }
+            far = plan(y, v, s, th, in);
+            ++i;
+        }
+        if (!in) {   // the last step left the shell: not one of this run
+            i -= 1;
+            break;
+        }
+        tally.acc += acc;
+        tally.rej += rej;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            x[a] = y[a];
+            u[a] = v[a];
+        }
+        if (i >= n) break;
+    }
+    tally.iters = tally.acc + tally.rej;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        t.x[a] = x[a];
+        t.u[a] = u[a];
+    }
+    t.nstep += (uint32_t)i;
+    return i;
+}
+
 }  // namespace gv
