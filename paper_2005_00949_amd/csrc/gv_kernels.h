@@ -818,18 +818,13 @@ __device__ __forceinline__ void store_child_q(const BatchArgs<P>& A, int q, uint
 template <int Q> __device__ __forceinline__ int is_q(int t) { return t == Q ? 1 : 0; }
 __device__ __forceinline__ int pick3(int q, const int v[3]) { return q == 0 ? v[0] : (q == 1 ? v[1] : v[2]); }
 
-// One chunk of BLOCK same-type tracks (TY known at compile time, so the
-// photon and charged-particle step paths are specialised): step each track up
-// to `inner` times in registers, stopping at its first secondary or its end;
-// then compact survivor + secondaries into the output queues.
 // Park one step at its RK45 move in the integration queue (lanes parking in
 // the same iteration reserve their slots with one atomic per wavefront).
-template <class P, int TY, class R = typename P::R>
-__device__ __forceinline__ void park_job(const BatchArgs<P>& A, const Track<P>& t, const Limits<R>& L, const Geo& G,
+template <class P, class R = typename P::R>
+__device__ __forceinline__ void park_job(const BatchArgs<P>& A, int ty, const Track<P>& t, const Limits<R>& L, const Geo& G,
                                          const Prop<R>& pr, double turns)
 {
-    static_assert(TY == kElectron || TY == kPositron, "only charged steps are parked");
-    constexpr int q = TY - 1;
+    const int q = ty - 1;
     const bool heavy = turns > kRkFirstTurns;
     const uint64_t pm = __ballot(1), hm = __ballot(heavy), lm = pm & ~hm;
     const int lane = threadIdx.x & 63;
@@ -881,13 +876,75 @@ __device__ __forceinline__ RkCounts rk_counts(const Ctrl* ctrl, int q, uint32_t 
 // there the wavefronts are sparse by nature and each launch is short.
 constexpr int kBulkMinLanes = 32;
 
-template <class P, int TY, int BLOCK, bool STABLE, bool INTEG, bool PARK = false, class R = typename P::R>
-__device__ __forceinline__ void process_chunk(const BatchArgs<P>& A, const Ctx<P>& c, uint32_t chunk, uint32_t base,
+// A pointer the compiler knows nothing about.  The addresses of the constants and
+// of the kernel arguments, and the seed, pass through an empty asm block wherever
+// a stage begins, so that the compiler reads what that stage needs of them in
+// that stage (scalar loads) instead of keeping every stage's uniform values
+// across the main loop: there are several times more of those than scalar
+// registers, and each spilled one costs a v_readlane per use (1,947 of them in
+// the mixed-precision step kernel; now 74).
+template <class T> __device__ __forceinline__ const T* opaque_ptr(const T* p)
+{
+    typedef const __attribute__((address_space(4))) T const_t;
+    const_t* q = (const_t*)p;
+    asm volatile("" : "+s"(q));
+    return (const T*)q;
+}
+// the step kernel's own arguments (its first and only one)
+template <class P> __device__ __forceinline__ const BatchArgs<P>& step_args()
+{
+    return *opaque_ptr((const BatchArgs<P>*)__builtin_amdgcn_kernarg_segment_ptr());
+}
+// the step context of one stage
+template <class P> __device__ __forceinline__ Ctx<P> stage_ctx(const TabView<typename P::R>& tv, uint64_t seed)
+{
+    uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)seed);
+    uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(seed >> 32));
+    asm volatile("" : "+s"(lo), "+s"(hi));
+    return Ctx<P>{((uint64_t)hi << 32) | lo, opaque_ptr(&c_geom), opaque_ptr(&c_phys), tv};
+}
+
+// the interaction or annihilation that step_to_interaction left (an annihilation
+// at rest comes before the step: no step is made)
+template <class P, bool PHOTON, class R = typename P::R>
+__device__ __forceinline__ void make_interaction(const Ctx<P>& c, const Sinks& S, DepCache& dc, Track<P>& t,
+                                                 StepOut<R>& o, int pend, DepAcc& acc, int& acc_vol)
+{
+    if (!PHOTON && pend == kPendAnnih) annihilate(c, t, o);
+    else interact(c, t, pend == kPendFirst, o);
+    t.nstep += o.did_step ? 1u : 0u;
+    if (PHOTON) {
+        if (o.vol_pre != acc_vol) {
+            dep_add(dc, S, t.ev, acc_vol, acc);
+            acc.e = 0.0;
+            acc.x = 0ull;
+            acc_vol = o.vol_pre;
+        }
+        acc_add(S, acc, o.edep);
+    }
+}
+
+// One chunk of BLOCK same-type tracks: photons, or (one code for both) electrons
+// or positrons, `ty`.  Each track is stepped up to `inner` times in registers,
+// stopping at its first secondary or its end; then survivors and secondaries are
+// compacted into the output queues.  Bound by issue: vector instructions were
+// issued in 71 % of the kernel's cycles (1,790 per wavefront and step, at 39 % of
+// the lanes; 3,000-event c4 batch), so instructions and lanes count.
+// In FP64 a track also stops at its first interaction, and all interactions of
+// the chunk are made at once after the loop, which otherwise runs every sampler
+// at every step for the few lanes that drew it: the shower phase of 1,250 c4
+// events 47.5 -> 41 ms.  Mixed precision, whose samplers are short, gains 2 %
+// there and loses 10 % on the barrel (lanes that end early), and samples in the
+// loop.
+template <class P, bool PHOTON, int BLOCK, bool STABLE, bool INTEG, bool PARK = false, class R = typename P::R>
+__device__ __forceinline__ void process_chunk(uint64_t seed, const int ty, uint32_t chunk, uint32_t base,
                                               uint32_t n_t, uint32_t epoch, int inner, ScanShared<BLOCK>& sh,
                                               DepCache& dc, unsigned* cnt_lds, uint32_t& steps_here,
                                               uint32_t& loads, uint32_t& stores, uint32_t n_chunks, RkSum& rks,
-                                              unsigned long long* lane_slots_lds, bool vac_ok, int min_lanes)
+                                              unsigned long long* lane_slots_lds, int min_lanes)
 {
+    constexpr bool kDefer = !P::kMixed;
+    const BatchArgs<P>& A = step_args<P>();
     const uint32_t slot = base + threadIdx.x;
     const bool active = slot < n_t;
     Track<P> t;
@@ -897,9 +954,10 @@ __device__ __forceinline__ void process_chunk(const BatchArgs<P>& A, const Ctx<P
     o.ch[0].type = -1;
     o.ch[1].type = -1;
     int iters = 0;
+    int pend = kPendNone;
     if (active) {
-        load_track(A.in[TY], slot, TY, t);
-        t.type = TY;
+        load_track(A.in[ty], slot, ty, t);
+        if (PHOTON) t.type = kGamma;
         loads += 1;
         DepAcc acc{0.0, 0ull};
         int acc_vol = t.vol;
@@ -908,72 +966,53 @@ __device__ __forceinline__ void process_chunk(const BatchArgs<P>& A, const Ctx<P
             // leaves the loop: they are queued as they stand and continue
             // in the next launch, and the wavefront takes its next chunk
             if (iters > 0 && __popcll(__ballot(1)) < min_lanes) break;
-            uint32_t ns = t.nstep;
-            const bool acc_empty = (acc.e == 0.0) & (acc.x == 0ull);
-            if (TY != kGamma && !INTEG && !PARK && vac_ok && __all((t.vol == 0) & acc_empty)) {
-                // A wavefront whose charged tracks are all in volumes without
-                // material (the loopers of a transport's low-population tail)
-                // steps them in the vacuum form of the step, here in the world
-                // volume and below in vacuum layers.  A step that leaves its
-                // track alive in vacuum changes nothing but the track (no
-                // deposit, process, secondary, counter or ledger entry; the
-                // deposit accumulator stays empty, so its volume does not
-                // matter), so such steps repeat with only the step count and
-                // the trace; the step that ends otherwise takes the
-                // bookkeeping below like any other.
-                const WorldRun<P> run = world_run(c, t);
-                for (;;) {
-                    step_world(c, run, t, o);
-                    steps_here += o.did_step;
-                    iters += 1;
-                    if (o.status != kAlive || t.vol != 0 || iters >= inner) break;
-                    if (A.S.trace && o.did_step) trace_step(A.S, t, o.vol_pre, t, o, ns);
-                    ns = t.nstep;
-                }
-            } else if (TY != kGamma && !INTEG && !PARK && vac_ok &&
-                       __all((vol_material(c_geom, t.vol) < 0) & acc_empty)) {
-                for (;;) {
-                    step_track<P, false, true>(c, t, o);
-                    steps_here += o.did_step;
-                    iters += 1;
-                    if (o.status != kAlive || iters >= inner) break;
-                    if (t.vol != o.vol_pre && vol_material(c_geom, t.vol) >= 0) break;
-                    if (A.S.trace && o.did_step) trace_step(A.S, t, o.vol_pre, t, o, ns);
-                    ns = t.nstep;
-                }
-            } else if (PARK && TY != kGamma) {
+            const BatchArgs<P>& A = step_args<P>();
+            const Ctx<P> c = stage_ctx<P>(A.tv, seed);
+            if (PARK && !PHOTON) {
                 Limits<R> L;
                 Geo G;
                 Prop<R> pr;
                 iters += 1;
                 if (step_track_park(c, t, o, L, G, pr)) {
-                    if constexpr (TY != kGamma) park_job<P, TY>(A, t, L, G, pr, rk_turns(pr.s, pr.rcurv));
+                    park_job<P>(A, ty, t, L, G, pr, rk_turns(pr.s, pr.rcurv));
                     atomicAdd(&cnt_lds[kCRkParked], 1u);
                     o.status = kParked;
                     break;
                 }
                 steps_here += o.did_step;
             } else {
-                step_track<P, INTEG>(c, t, o);
+                step_to_interaction<P, PHOTON, INTEG>(c, t, o, pend);
                 steps_here += o.did_step;
                 iters += 1;
             }
-            if (TY != kGamma) {
+            if constexpr (!PHOTON) {   // (a photon deposits in its interaction only)
                 rks.acc += (uint32_t)o.rk.acc;
                 rks.rej += (uint32_t)o.rk.rej;
                 rks.slots += (uint32_t)o.rk.iters;
+                if (o.vol_pre != acc_vol) {
+                    dep_add(dc, A.S, t.ev, acc_vol, acc);
+                    acc.e = 0.0;
+                    acc.x = 0ull;
+                    acc_vol = o.vol_pre;
+                }
+                acc_add(A.S, acc, o.edep);
             }
-            if (o.vol_pre != acc_vol) {
-                dep_add(dc, A.S, t.ev, acc_vol, acc);
-                acc.e = 0.0;
-                acc.x = 0ull;
-                acc_vol = o.vol_pre;
+            if constexpr (!kDefer) {
+                if (pend != kPendNone) make_interaction<P, PHOTON>(c, A.S, dc, t, o, pend, acc, acc_vol);
+                pend = kPendNone;
             }
-            acc_add(A.S, acc, o.edep);
-            if (A.S.trace && o.did_step) trace_step(A.S, t, o.vol_pre, t, o, ns);
+            if (pend != kPendNone) break;
+            if (A.S.trace && o.did_step) trace_step(A.S, t, o.vol_pre, t, o, t.nstep - 1u);
             account_rare(A.S, t.ev, o, cnt_lds);
-            if (o.status == kEscaped) escape_count(A.S, TY, t.T, t.u[2]);
+            if (o.status == kEscaped) escape_count(A.S, ty, t.T, t.u[2]);
             if (o.status != kAlive || o.nchild > 0) break;
+        }
+        const BatchArgs<P>& A = step_args<P>();
+        if (kDefer && pend != kPendNone) {
+            const Ctx<P> c = stage_ctx<P>(A.tv, seed);
+            make_interaction<P, PHOTON>(c, A.S, dc, t, o, pend, acc, acc_vol);
+            if (A.S.trace && o.did_step) trace_step(A.S, t, o.vol_pre, t, o, t.nstep - 1u);
+            account_rare(A.S, t.ev, o, cnt_lds);
         }
         dep_add(dc, A.S, t.ev, acc_vol, acc);
     }
@@ -984,30 +1023,31 @@ __device__ __forceinline__ void process_chunk(const BatchArgs<P>& A, const Ctx<P
         for (int off = 32; off > 0; off >>= 1) m = max(m, __shfl_xor(m, off, 64));
         if ((threadIdx.x & 63) == 0 && m) atomicAdd(lane_slots_lds, 64ull * (unsigned)m);
     }
-    dep_flush<BLOCK>(dc, A.S);
+    const BatchArgs<P>& A1 = step_args<P>();
+    dep_flush<BLOCK>(dc, A1.S);
     const int alive = (active && o.status == kAlive) ? 1 : 0;
     const int q1 = o.nchild > 0 ? o.ch[0].type : -1;
     const int q2 = o.nchild > 1 ? o.ch[1].type : -1;
     int cnt[3];
-    cnt[0] = (TY == 0 ? alive : 0) + is_q<0>(q1) + is_q<0>(q2);
-    cnt[1] = (TY == 1 ? alive : 0) + is_q<1>(q1) + is_q<1>(q2);
-    cnt[2] = (TY == 2 ? alive : 0) + is_q<2>(q1) + is_q<2>(q2);
+    cnt[0] = (ty == 0 ? alive : 0) + is_q<0>(q1) + is_q<0>(q2);
+    cnt[1] = (ty == 1 ? alive : 0) + is_q<1>(q1) + is_q<1>(q2);
+    cnt[2] = (ty == 2 ? alive : 0) + is_q<2>(q1) + is_q<2>(q2);
     int excl[3], tot[3];
     block_scan3<BLOCK>(cnt, excl, tot, sh);
     if (STABLE) lookback3<BLOCK>(A.status, chunk, epoch, tot, sh, &A.ctrl->overflow);
     else reserve3<BLOCK>(&A.ctrl->count[A.parity ^ 1][0], A.cap, tot, sh, &A.ctrl->overflow);
     // output positions in expanded order: survivor, child 0, child 1
     if (alive) {
-        const uint32_t pos = (uint32_t)sh.prefix[TY] + (uint32_t)excl[TY];
+        const uint32_t pos = (uint32_t)sh.prefix[ty] + (uint32_t)pick3(ty, excl);
         if (pos < A.cap) {
-            store_track(A.out[TY], pos, t);
+            store_track(A.out[ty], pos, t);
             stores += 1;
         } else {
             atomicOr(&A.ctrl->overflow, 1u);
         }
     }
     if (q1 >= 0) {
-        const uint32_t pos = (uint32_t)sh.prefix[q1] + (uint32_t)pick3(q1, excl) + (uint32_t)((q1 == TY) & alive);
+        const uint32_t pos = (uint32_t)sh.prefix[q1] + (uint32_t)pick3(q1, excl) + (uint32_t)((q1 == ty) & alive);
         if (pos < A.cap) {
             store_child_q(A, q1, pos, t, o.ch[0]);
             stores += 1;
@@ -1017,7 +1057,7 @@ __device__ __forceinline__ void process_chunk(const BatchArgs<P>& A, const Ctx<P
     }
     if (q2 >= 0) {
         const uint32_t pos = (uint32_t)sh.prefix[q2] + (uint32_t)pick3(q2, excl) +
-                             (uint32_t)((q2 == TY) & alive) + (uint32_t)(q2 == q1);
+                             (uint32_t)((q2 == ty) & alive) + (uint32_t)(q2 == q1);
         if (pos < A.cap) {
             store_child_q(A, q2, pos, t, o.ch[1]);
             stores += 1;
@@ -1035,13 +1075,14 @@ __device__ __forceinline__ void process_chunk(const BatchArgs<P>& A, const Ctx<P
 // INTEG: field integrators compiled in (field_method RK4 / RK45); the helix
 // variant leaves them out and keeps its register budget.  PARK (without
 // INTEG): the integration queue's step kernel, which parks every charged move
-// in a field and so has the helix variant's register budget.  The mixed-precision
-// helix variant is held to three wavefronts per SIMD (168 VGPRs): the step
-// chain is latency-bound, and a third resident wavefront hides more of it.
+// in a field and so has the helix variant's register budget.  That budget is
+// four wavefronts per SIMD in mixed precision (128 VGPRs; 7 % faster than three)
+// and two in FP64 (256; one without it), at the price of a few spills.
 template <class P, int BLOCK, bool STABLE, bool INTEG, bool PARK = false>
-__global__ void __launch_bounds__(BLOCK, (!INTEG && sizeof(typename P::R) == sizeof(float)) ? 3 : 1)
-k_step_batched(BatchArgs<P> A)
+__global__ void __launch_bounds__(BLOCK, (!INTEG && sizeof(typename P::R) == sizeof(float)) ? 4 : !INTEG ? 2 : 1)
+k_step_batched(BatchArgs<P>)
 {
+    const BatchArgs<P>& A = step_args<P>();
     __shared__ ScanShared<BLOCK> sh;
     __shared__ unsigned cnt_lds[kNCount];
     __shared__ unsigned long long rk_lds[4];
@@ -1074,8 +1115,8 @@ k_step_batched(BatchArgs<P> A)
     for (int i = threadIdx.x; i < kNCount; i += BLOCK) cnt_lds[i] = 0;
     if (threadIdx.x < 4) rk_lds[threadIdx.x] = 0ull;
     dep_clear<BLOCK>(dc);
-    Ctx<P> c{A.ctrl->seed, &c_geom, &c_phys, A.tv};
-    const bool vac_ok = c_geom.field_map == kMapUniform;
+    const uint64_t seed = A.ctrl->seed;
+    const int min_lanes = A.min_lanes;
     uint32_t steps_g = 0, steps_e = 0, steps_p = 0;
     uint32_t loads = 0, stores = 0;
     RkSum rks{0u, 0u, 0u};
@@ -1089,18 +1130,19 @@ k_step_batched(BatchArgs<P> A)
         if (first >= n_chunks) break;
         const uint32_t last = min(first + (uint32_t)A.basket_chunks, n_chunks);
         for (uint32_t chunk = first; chunk < last; ++chunk) {
-            if (chunk < c0)
-                process_chunk<P, kGamma, BLOCK, STABLE, INTEG, PARK>(A, c, chunk, chunk * BLOCK, n0, epoch, inner, sh, dc,
-                                                                     cnt_lds, steps_g, loads, stores, n_chunks, rks,
-                                                                     &rk_lds[3], vac_ok, A.min_lanes);
-            else if (chunk < c0 + c1)
-                process_chunk<P, kElectron, BLOCK, STABLE, INTEG, PARK>(A, c, chunk, (chunk - c0) * BLOCK, n1, epoch, inner,
-                                                                        sh, dc, cnt_lds, steps_e, loads, stores, n_chunks,
-                                                                        rks, &rk_lds[3], vac_ok, A.min_lanes);
-            else
-                process_chunk<P, kPositron, BLOCK, STABLE, INTEG, PARK>(A, c, chunk, (chunk - c0 - c1) * BLOCK, n2, epoch,
-                                                                        inner, sh, dc, cnt_lds, steps_p, loads, stores,
-                                                                        n_chunks, rks, &rk_lds[3], vac_ok, A.min_lanes);
+            if (chunk < c0) {
+                process_chunk<P, true, BLOCK, STABLE, INTEG, PARK>(seed, kGamma, chunk, chunk * BLOCK, n0, epoch, inner,
+                                                                   sh, dc, cnt_lds, steps_g, loads, stores, n_chunks,
+                                                                   rks, &rk_lds[3], min_lanes);
+            } else {
+                const bool ele = chunk < c0 + c1;
+                uint32_t n = 0;
+                process_chunk<P, false, BLOCK, STABLE, INTEG, PARK>(
+                    seed, ele ? kElectron : kPositron, chunk, (ele ? chunk - c0 : chunk - c0 - c1) * BLOCK,
+                    ele ? n1 : n2, epoch, inner, sh, dc, cnt_lds, n, loads, stores, n_chunks, rks, &rk_lds[3], min_lanes);
+                steps_e += ele ? n : 0u;
+                steps_p += ele ? 0u : n;
+            }
         }
     }
     atomicAdd(&cnt_lds[kCSteps + kGamma], steps_g);

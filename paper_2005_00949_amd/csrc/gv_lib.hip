@@ -1064,7 +1064,16 @@ template <class P> void launch_pool_helper(int parity, hipStream_t s)
 // that fill the GPU (the tail threshold and above) run in the step kernel's
 // bulk graph, which starts and ends at parity 0; so pool launches come in
 // pairs.
-template <class P> int run_pool_window(size_t b, size_t e, uint64_t seed, const Tuning& tu)
+// A trial of the autotuner takes the bulk replays alone (its knobs have no part
+// in the pool kernel): their time and steps go to `bulk_only`, and the window is
+// left once its population has fallen below the tail threshold.
+struct BulkRate {
+    double ms = 0.0;
+    unsigned long long steps = 0;
+};
+
+template <class P>
+int run_pool_window(size_t b, size_t e, uint64_t seed, const Tuning& tu, BulkRate* bulk_only = nullptr)
 {
     QueueMem<P>& Q = batch_queues<P>();
     uint32_t counts[3];
@@ -1083,6 +1092,7 @@ template <class P> int run_pool_window(size_t b, size_t e, uint64_t seed, const 
     int64_t tail_steps0 = 0;
     while (n > 0) {
         const bool tail = n < tu.tail && (peak >= tu.tail || !grew);
+        if (tail && bulk_only) return GV_OK;
         if (tail && !in_tail) {
             in_tail = true;
             tail_steps0 = (int64_t)steps;
@@ -1134,6 +1144,10 @@ template <class P> int run_pool_window(size_t b, size_t e, uint64_t seed, const 
             std::fprintf(stderr, "[gv] %s%s%s: %.3f ms, population %u/%u/%u, vacuum %u, steps %llu\n",
                          bulk ? "bulk" : "pool", helper ? " helper" : "", tail ? " tail" : "", ms, m.count[0], m.count[1],
                          m.count[2], m.n_vac, m.steps - steps);
+        if (bulk && bulk_only) {
+            bulk_only->ms += ms;
+            bulk_only->steps += m.steps - steps;
+        }
         steps = m.steps;
         n_gamma = m.count[0];
         n_vac = m.n_vac;
@@ -1252,7 +1266,10 @@ int reset_run_buffers(int64_t n_events)
 // Autotuner for the knobs the caller left at 0 (basket, occupancy, inner
 // steps).  Trial transports of a sample of the staged batch (its first
 // events, at least 1024 primaries, about an eighth of the batch) are timed by
-// step-kernel time; coordinate search over inner steps, then basket, then
+// step-kernel time; with the pool driver half of the batch, of which only the
+// bulk replays are run and timed (an eighth with its tail preferred two
+// workgroups per CU on some runs, 111 ms for the shower phase of the c4 batch
+// against 90 with four); coordinate search over inner steps, then basket, then
 // occupancy, from the defaults; a candidate replaces the incumbent only if it
 // is at least 3 % faster.  The choice is cached per precision, queue order and
 // batch-size class; the trials' deposits and counters are discarded.
@@ -1272,7 +1289,7 @@ template <class P> int tuned_choice(int64_t n_events, uint64_t seed, std::array<
         return GV_OK;
     }
     const double t0 = now_ms();
-    int64_t ne = std::max<int64_t>(1, n_events / 8);
+    int64_t ne = std::max<int64_t>(1, n_events / (pool_mode() ? 2 : 8));
     while (ne < n_events && L.ev_start[ne] < 1024) ne = std::min(n_events, 2 * ne);
     const size_t cap = batch_cap<P>();
     const uint64_t tseed = seed ^ 0x6175746f74756e65ull;
@@ -1284,7 +1301,8 @@ template <class P> int tuned_choice(int64_t n_events, uint64_t seed, std::array<
         if (rc) return rc;
         L.stats.iterations = 0;
         const double k0 = L.stats.kernel_ms;
-        rc = pool_mode() ? run_pool_window<P>(L.ev_start[0], L.ev_start[ne], tseed, tu)
+        BulkRate bulk;
+        rc = pool_mode() ? run_pool_window<P>(L.ev_start[0], L.ev_start[ne], tseed, tu, &bulk)
                          : run_batched_window<P>(L.ev_start[0], L.ev_start[ne], tseed, tu);
         if (rc == GV_E_CAPACITY) {
             rate = 0.0;
@@ -1295,7 +1313,8 @@ template <class P> int tuned_choice(int64_t n_events, uint64_t seed, std::array<
         HIPCHK(hipMemcpyAsync(cnt, L.counters.p, sizeof(cnt), hipMemcpyDeviceToHost, stream()));
         HIPCHK(hipStreamSynchronize(stream()));
         const double ms = L.stats.kernel_ms - k0;
-        rate = ms > 0.0 ? (double)(cnt[kCSteps] + cnt[kCSteps + 1] + cnt[kCSteps + 2]) / ms : 0.0;
+        if (pool_mode()) rate = bulk.ms > 0.0 ? (double)bulk.steps / bulk.ms : 0.0;
+        else rate = ms > 0.0 ? (double)(cnt[kCSteps] + cnt[kCSteps + 1] + cnt[kCSteps + 2]) / ms : 0.0;
         if (L.progress)
             std::fprintf(stderr, "[gv] autotune basket %d occupancy %d inner %d: %.4g steps/ms\n", c[0], c[1], c[2],
                          rate);

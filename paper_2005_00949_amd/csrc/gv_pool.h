@@ -473,29 +473,14 @@ __device__ __forceinline__ int pool_vacuum(const PoolArgs<P>& A, const Ctx<P>& c
     return tag;
 }
 
-// The step context of one stage.  The addresses of the constants and the seed
-// pass through an empty asm block, so that the compiler reads what a stage needs
-// of them in that stage (scalar loads) instead of keeping every stage's uniform
-// values across the main loop: there are several times more of those than
-// scalar registers, and each spilled one costs a v_readlane per use.
-template <class T> __device__ __forceinline__ const T* pool_opaque(const T* p)
-{
-    typedef const __attribute__((address_space(4))) T const_t;
-    const_t* q = (const_t*)p;
-    asm volatile("" : "+s"(q));
-    return (const T*)q;
-}
-// ... and so do the kernel's own arguments (its first and only one)
+// the kernel's own arguments (its first and only one; see opaque_ptr)
 template <class P> __device__ __forceinline__ const PoolArgs<P>& pool_args()
 {
-    return *pool_opaque((const PoolArgs<P>*)__builtin_amdgcn_kernarg_segment_ptr());
+    return *opaque_ptr((const PoolArgs<P>*)__builtin_amdgcn_kernarg_segment_ptr());
 }
 template <class P> __device__ __forceinline__ Ctx<P> pool_ctx(const PoolArgs<P>& A, uint64_t seed)
 {
-    uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)seed);
-    uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(seed >> 32));
-    asm volatile("" : "+s"(lo), "+s"(hi));
-    return Ctx<P>{((uint64_t)hi << 32) | lo, pool_opaque(&c_geom), pool_opaque(&c_phys), A.tv};
+    return stage_ctx<P>(A.tv, seed);
 }
 
 // the tag of a track that waits for its next step

@@ -591,6 +591,54 @@ __device__ inline void step_track(const Ctx<P>& c, Track<P>& t, StepOut<R>& o)
     step_after_move(c, t, L, G, pr, o);
 }
 
+// The same step up to its discrete interaction or annihilation, which is left
+// in `pend` for the caller (interact or annihilate, then nstep + 1 if a step was
+// made); PHOTON: the track is a photon, else it is charged.  An interaction of a
+// charged track and an annihilation deposit nothing, and a photon deposits in
+// its interaction only, so o.edep is whole either way.
+enum : int { kPendNone = 0, kPendFirst = 1, kPendSecond = 2, kPendAnnih = 3 };
+
+template <class P, bool PHOTON, bool INTEG, class R = typename P::R>
+__device__ __forceinline__ void step_to_interaction(const Ctx<P>& c, Track<P>& t, StepOut<R>& o, int& pend)
+{
+    init_out(t, o);
+    if (!PHOTON && t.vol != kOutside && t.T < (R)c.ph->t_track) {   // stage_prestep below the tracking cut
+        o.edep += (double)t.T;
+        t.T = (R)0;
+        o.status = kDead;
+        pend = t.type == kPositron ? kPendAnnih : kPendNone;
+        return;
+    }
+    if (!stage_prestep(c, t, o)) return;
+    Limits<R> L;
+    stage_limit(c, t, L);
+    Geo G;
+    stage_geom(c, t, G);
+    Prop<R> pr;
+    stage_move<P, INTEG>(c, t, L, G, pr);
+    o.did_step = 1;
+    o.s = pr.s;
+    o.lim = pr.lim;
+    o.rk = pr.rk;
+    bool stopped = false;
+    if (!PHOTON) {
+        stage_msc(c, t, L, pr);
+        stopped = stage_eloss(c, t, L, pr, o);
+    }
+    if (stopped) {
+        o.status = kDead;
+        pend = t.type == kPositron ? kPendAnnih : kPendNone;
+        if (t.type == kPositron) return;
+    } else if (pr.lim == kLimPhys && !pr.crossed) {
+        pend = L.usel * L.stot < L.sa ? kPendFirst : kPendSecond;
+        return;
+    } else if (t.vol == kOutside) {
+        o.e_escaped += (double)t.T;
+        o.status = kEscaped;
+    }
+    t.nstep += 1;
+}
+
 // The same step ended after one of its stages (Sec. 2.1.2), for the
 // per-stage test entry: s_phys and the continuous-loss length after
 // ComputeIntLen, then the boundary distance and safety, then the step length,
