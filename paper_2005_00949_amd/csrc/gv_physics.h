@@ -74,24 +74,57 @@ __device__ __forceinline__ const R* tab_base(const TabView<R>& tv, int m, int ty
     return tv.rec + (size_t)(m * 3 + type) * tv.n * kCols;
 }
 
-// inverse of the linearly interpolated range: the kinetic energy at range r
+// one record (16-byte aligned: records are kCols values from an aligned start),
+// in wide loads: a load of scattered records is bound by their number, not their size
+__device__ __forceinline__ void load_row(const float* base, int i, float y[kCols])
+{
+    const float4 v = *reinterpret_cast<const float4*>(base + (size_t)i * kCols);
+    y[0] = v.x;
+    y[1] = v.y;
+    y[2] = v.z;
+    y[3] = v.w;
+}
+__device__ __forceinline__ void load_row(const double* base, int i, double y[kCols])
+{
+    const double2* p = reinterpret_cast<const double2*>(base + (size_t)i * kCols);
+    const double2 a = p[0], b = p[1];
+    y[0] = a.x;
+    y[1] = a.y;
+    y[2] = b.x;
+    y[3] = b.y;
+}
+
+// Inverse of the linearly interpolated range: the kinetic energy at range r.
+// lo: any guess of the bin; the bin is found from there, range by range (ranges
+// increase strictly, so it is the one a search over the table finds; that took
+// ten dependent loads of scattered records per step, a close guess takes two).
 template <class R>
-__device__ inline R range_inverse(const TabView<R>& tv, const R* base, R r)
+__device__ inline R range_inverse(const TabView<R>& tv, const R* base, R r, int lo)
 {
     const int n = tv.n;
-    if (r <= base[3]) return tv.E[0] * r / base[3];
-    int lo = 0, hi = n - 1;
-    if (r >= base[(n - 1) * kCols + 3]) {
-        lo = n - 2;
-    } else {
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (base[mid * kCols + 3] <= r) lo = mid;
-            else hi = mid;
-        }
+    lo = lo < 0 ? 0 : (lo > n - 2 ? n - 2 : lo);
+    R r0 = base[lo * kCols + 3], r1 = base[(lo + 1) * kCols + 3];
+    while (lo > 0 && r0 > r) {
+        --lo;
+        r1 = r0;
+        r0 = base[lo * kCols + 3];
     }
-    const R r0 = base[lo * kCols + 3], r1 = base[(lo + 1) * kCols + 3];
+    while (lo < n - 2 && r1 <= r) {
+        ++lo;
+        r0 = r1;
+        r1 = base[(lo + 1) * kCols + 3];
+    }
+    if (lo == 0 && r <= r0) return tv.E[0] * r / r0;
     return tv.E[lo] + (tv.E[lo + 1] - tv.E[lo]) * (r - r0) / (r1 - r0);
+}
+
+// The guess: near a point of the table, range grows as a power of the kinetic
+// energy T with exponent d ln R / d ln T = T / (S R), and nodes are spaced evenly
+// in log T.  x: fractional node of T.
+__device__ __forceinline__ int range_bin_guess(float x, float T, float dedx, float range, float r, float bpd)
+{
+    const float d = bpd * 0.30102999f * (dedx * range / T) * __log2f(r / range);
+    return (int)fminf(fmaxf(x + d, 0.0f), 1.0e6f);
 }
 
 // ---------------------------------------------------------------------------

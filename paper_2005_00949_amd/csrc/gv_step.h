@@ -65,6 +65,8 @@ template <class R> struct Limits {
     R range;
     R stot, sa;
     R usel;
+    R dedx;     // restricted stopping power (charged)
+    R node;     // fractional table node of the kinetic energy (charged)
     int m;      // material of the pre-step volume (-1 vacuum)
 };
 
@@ -198,6 +200,8 @@ __device__ inline void stage_limit(const Ctx<P>& c, const Track<P>& t, Limits<R>
     L.range = (R)0;
     L.s_eloss = big_len<R>();
     L.usel = (R)0;
+    L.dedx = (R)0;
+    L.node = (R)0;
     L.s_phys = big_len<R>();
     // vacuum has no process: its STEP block is never needed (the streams are
     // counter-based, so not drawing it changes no other number)
@@ -208,11 +212,16 @@ __device__ inline void stage_limit(const Ctx<P>& c, const Track<P>& t, Limits<R>
         const R* base = tab_base(c.tv, m, t.type);
         const int i = find_bin(c.tv, t.T, c.ph->log10_emin, c.ph->bpd);
         const R w = (t.T - c.tv.E[i]) / (c.tv.E[i + 1] - c.tv.E[i]);
-        L.sa = lerp_col(c.tv, base, i, 0, w);
-        const R sb = lerp_col(c.tv, base, i, 1, w);
+        R y0[kCols], y1[kCols];
+        load_row(base, i, y0);
+        load_row(base, i + 1, y1);
+        L.sa = y0[0] + (y1[0] - y0[0]) * w;
+        const R sb = y0[1] + (y1[1] - y0[1]) * w;
         L.stot = L.sa + sb;
         if (t.type != kGamma) {
-            L.range = lerp_col(c.tv, base, i, 3, w);
+            L.dedx = y0[2] + (y1[2] - y0[2]) * w;
+            L.range = y0[3] + (y1[3] - y0[3]) * w;
+            L.node = (R)i + w;
             L.s_eloss = L.range <= (R)0.1 ? L.range : m_max((R)0.2 * L.range, (R)0.1);
         }
     }
@@ -400,11 +409,12 @@ __device__ inline bool stage_eloss(const Ctx<P>& c, Track<P>& t, const Limits<R>
     const R s = (R)pr.s;
     R dE;
     if (s < (R)0.01 * L.range) {
-        const int i = find_bin(c.tv, Tp, c.ph->log10_emin, c.ph->bpd);
-        const R w = (Tp - c.tv.E[i]) / (c.tv.E[i + 1] - c.tv.E[i]);
-        dE = lerp_col(c.tv, base, i, 2, w) * s;
+        dE = L.dedx * s;   // (no stage since ComputeIntLen has changed the energy)
     } else {
-        dE = Tp - range_inverse(c.tv, base, L.range - s);
+        const R r = L.range - s;
+        dE = Tp - range_inverse(c.tv, base, r,
+                                range_bin_guess((float)L.node, (float)Tp, (float)L.dedx, (float)L.range, (float)r,
+                                                (float)c.ph->bpd));
     }
     const R rtrack = P::kMixed ? (R)c.ph->r_track_f[L.m][t.type == kPositron] : (R)c.ph->r_track[L.m][t.type == kPositron];
     bool stopped = false;
