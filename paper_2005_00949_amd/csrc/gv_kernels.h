@@ -882,7 +882,7 @@ constexpr int kBulkMinLanes = 32;
 // that stage (scalar loads) instead of keeping every stage's uniform values
 // across the main loop: there are several times more of those than scalar
 // registers, and each spilled one costs a v_readlane per use (1,947 of them in
-// the mixed-precision step kernel; now 74).
+// the mixed-precision step kernel; now 67).
 template <class T> __device__ __forceinline__ const T* opaque_ptr(const T* p)
 {
     typedef const __attribute__((address_space(4))) T const_t;

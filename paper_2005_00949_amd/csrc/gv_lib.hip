@@ -1480,13 +1480,19 @@ __global__ void k_na_clear(uint32_t* counts)
     if (threadIdx.x < 4) counts[threadIdx.x] = 0;
 }
 
+constexpr int64_t kNaOneLaunch = (int64_t)1 << 13;   // up to here one launch (kernels' comment)
+
 template <int ITEMS, bool ALIGNED>
 void launch_part(const int8_t* codes, int64_t n, int32_t* index, uint32_t* counts, unsigned long long* totals,
                  hipStream_t s)
 {
     const unsigned grid = (unsigned)((n + ITEMS * kPartBlock - 1) / (ITEMS * kPartBlock));
+    if (ITEMS == 4 && n <= kNaOneLaunch) {
+        k_part_place<4, ALIGNED, true><<<grid, kPartBlock, 0, s>>>(codes, n, index, counts, totals);
+        return;
+    }
     k_part_count<ITEMS, ALIGNED><<<grid, kPartBlock, 0, s>>>(codes, n, totals);
-    k_part_place<ITEMS, ALIGNED><<<grid, kPartBlock, 0, s>>>(codes, n, index, counts, totals);
+    k_part_place<ITEMS, ALIGNED, false><<<grid, kPartBlock, 0, s>>>(codes, n, index, counts, totals);
 }
 }  // namespace
 

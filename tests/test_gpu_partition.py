@@ -1,7 +1,8 @@
-"""gv_compact3_noalloc at the sizes where its two launches can go wrong: one
+"""gv_compact3_noalloc at the sizes where its launches can go wrong: one
 input, the edges of a thread's and a block's share (4 and 16 inputs, 1,024 and
-4,096), both sides of the size where the share changes (2^20), the largest call
-(2^24), and codes at addresses that rule out wide loads.  Whole numbers, against
+4,096), both sides of the sizes where one launch becomes two (2^13) and where the
+share changes (2^20), the largest call (2^24), and codes at addresses that rule
+out wide loads.  Whole numbers, against
 numpy: no tolerance."""
 import ctypes as C
 
@@ -14,8 +15,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("offset", [0, 1, 4])
-@pytest.mark.parametrize("n", [1, 3, 4, 5, 1023, 1024, 1025, 4096, 262145, (1 << 20) - 1, 1 << 20, (1 << 20) + 4097,
-                               (1 << 24) - 15, 1 << 24])
+@pytest.mark.parametrize("n", [1, 3, 4, 5, 1023, 1024, 1025, 4096, 4097, 8191, 8192, 8193, 32769, 262145, (1 << 20) - 1,
+                               1 << 20, (1 << 20) + 4097, (1 << 24) - 15, 1 << 24])
 def test_queues_and_counts(n, offset):
     import paper_2005_00949_amd as gv
     if n > 1 << 21 and offset == 4:
