@@ -822,15 +822,15 @@ template <class P> QueueMem<P>& batch_queues();
 template <> QueueMem<P64>& batch_queues<P64>() { return L.q64; }
 template <> QueueMem<PMix>& batch_queues<PMix>() { return L.qmix; }
 
-// capture K launches alternating parity (K even: a replay ends where it began);
-// tail: the tail graph, with the vacuum helper before each step launch and,
-// for RK45 with arrival order, integration inside the step only
 // vacuum steps per track and helper launch in the tail replays
 constexpr int kVacHelperSteps = 4096;
 // its blocks there, for 256 loopers (most of its launches find material and leave;
 // the pool driver, which launches it only for loopers, gives it a block per CU)
 constexpr int kVacHelperGraphGrid = 64;
 
+// capture K launches alternating parity (K even: a replay ends where it began);
+// tail: the tail graph, with the vacuum helper before each step launch and,
+// for RK45 with arrival order, integration inside the step only
 template <class P>
 int capture(const Tuning& tu, int grid, int K, int inner_bulk, int inner_tail, bool tail, hipGraph_t* g,
             hipGraphExec_t* ge)
@@ -884,21 +884,10 @@ int capture(const Tuning& tu, int grid, int K, int inner_bulk, int inner_tail, b
     return GV_OK;
 }
 
-template <class P> int build_graph(const Tuning& tu, const GraphKey& key)
-{
-    drop_graph();
-    int rc = capture<P>(tu, tu.occupancy * L.n_cu, tu.K, tu.inner_bulk, tu.inner_tail, false, &L.graph, &L.gexec);
-    if (rc) return rc;
-    // the vacuum helper steps the last loopers of the tail replays (with the
-    // looper forms of the helix in a uniform field, else the general step)
-    rc = capture<P>(tu, tu.tail_grid, tu.tail_K, tu.inner_tail, tu.inner_tail, true, &L.graph_tail, &L.gexec_tail);
-    if (rc) return rc;
-    L.gkey = key;
-    return GV_OK;
-}
-
-// the step kernel's graphs for the current options, captured if they are not there
-template <class P> int ensure_bulk_graph(const Tuning& tu)
+// the step kernel's graphs for the current options, captured if they are not
+// there; with_tail: the tail graph too (the pool driver replays the bulk graph
+// alone, and a tail graph is another 64 step and 64 helper launches to capture)
+template <class P> int ensure_graphs(const Tuning& tu, bool with_tail)
 {
     QueueMem<P>& Q = batch_queues<P>();
     GraphKey key;
@@ -920,8 +909,20 @@ template <class P> int ensure_bulk_graph(const Tuning& tu)
     key.grid = tu.occupancy * L.n_cu;
     key.tail_grid = tu.tail_grid;
     key.tail_K = tu.tail_K;
-    if (L.gexec && L.gkey == key) return GV_OK;
-    return build_graph<P>(tu, key);
+    if (!(L.gkey == key)) drop_graph();
+    if (!L.gexec) {
+        int rc = capture<P>(tu, tu.occupancy * L.n_cu, tu.K, tu.inner_bulk, tu.inner_tail, false, &L.graph, &L.gexec);
+        if (rc) return rc;
+    }
+    // the vacuum helper steps the last loopers of the tail replays (with the
+    // looper forms of the helix in a uniform field, else the general step)
+    if (with_tail && !L.gexec_tail) {
+        int rc = capture<P>(tu, tu.tail_grid, tu.tail_K, tu.inner_tail, tu.inner_tail, true, &L.graph_tail,
+                            &L.gexec_tail);
+        if (rc) return rc;
+    }
+    L.gkey = key;
+    return GV_OK;
 }
 
 // batched transport of one event window; returns GV_E_CAPACITY on overflow
@@ -934,7 +935,7 @@ template <class P> int run_batched_window(size_t b, size_t e, uint64_t seed, con
     if (rc) return rc;
     rc = upload_ctrl(counts, seed);
     if (rc) return rc;
-    rc = ensure_bulk_graph<P>(tu);
+    rc = ensure_graphs<P>(tu, true);
     if (rc) return rc;
     hipStream_t s = stream();
     uint32_t population = counts[0] + counts[1] + counts[2];
@@ -1101,7 +1102,7 @@ int run_pool_window(size_t b, size_t e, uint64_t seed, const Tuning& tu, BulkRat
         const bool helper = !bulk && n_vac == n && n_gamma == 0 && n <= (uint32_t)(L.n_cu * kVacHelperWaves);
         int K = 1;
         if (bulk) {   // captured, if need be, before the interval that counts as kernel time
-            rc = ensure_bulk_graph<P>(tu);
+            rc = ensure_graphs<P>(tu, false);
             if (rc) return rc;
         }
         HIPCHK(hipEventRecord(L.ev0, s));
