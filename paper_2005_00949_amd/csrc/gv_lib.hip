@@ -213,8 +213,14 @@ struct Lib {
     size_t staged_b = 0, staged_e = 0;   // window whose queue slots are on the device
     bool staged_one_queue = false;       // ... laid out for one mixed pool (plain) or per type
     // autotuner choices, per (precision, queue order, log2 of the batch size);
-    // cleared by gv_init
-    std::map<std::tuple<int, int, int>, std::array<int, 3>> tune_cache;
+    // cleared by gv_init.  measured: false if the sample had no step-kernel work
+    // to time, and the defaults stand
+    struct TuneEntry {
+        std::array<int, 3> choice;
+        bool measured;
+    };
+    std::map<std::tuple<int, int, int>, TuneEntry> tune_cache;
+    uint32_t peak = 0;   // largest population the pool driver has seen in this transport
     double autotune_ms = 0.0;
     bool tuned = false;
 };
@@ -539,6 +545,17 @@ int apply_run_params()
 
 // ---- transport helpers ----------------------------------------------------
 
+// The pool kernel takes part in transports whose knobs are all left to the
+// library: a caller that sets one asks for the step kernel it describes, a
+// trace records whole steps, and an explicit capacity bounds the step kernel's
+// queue use.
+bool pool_mode()
+{
+    const gv_config& c = L.cfg;
+    return c.driver == GV_DRIVER_BATCHED && c.trace_cap == 0 && c.capacity == 0 && !c.basket && !c.occupancy &&
+           !c.inner_steps && !c.graph_steps;
+}
+
 struct Tuning {
     int block, chunks, occupancy, inner_bulk, inner_tail, K;
     uint32_t tail;       // population below which the tail graph runs
@@ -562,7 +579,9 @@ Tuning pick_tuning(const std::array<int, 3>& choice)
     t.inner_bulk = L.cfg.inner_steps ? L.cfg.inner_steps : choice[2];
     t.inner_tail = std::max(t.inner_bulk, 256);
     t.K = L.cfg.graph_steps ? L.cfg.graph_steps : 16;
-    t.tail = (uint32_t)std::min<long long>((long long)L.n_cu * t.block * 2, 1u << 30);
+    // two baskets per CU; where the pool kernel takes the populations below, two
+    // of 256 tracks whatever the basket (gv_pool.h says why the line lies there)
+    t.tail = (uint32_t)std::min<long long>((long long)L.n_cu * (pool_mode() ? 256 : t.block) * 2, 1u << 30);
     t.tail_grid = t.occupancy * L.n_cu;
     t.tail_K = 4 * t.K;
     return t;
@@ -999,17 +1018,6 @@ template <class P> int run_batched_window(size_t b, size_t e, uint64_t seed, con
 
 // ---- the pool kernel's driver ----------------------------------------------
 
-// The pool kernel takes part in transports whose knobs are all left to the
-// library: a caller that sets one asks for the step kernel it describes, a
-// trace records whole steps, and an explicit capacity bounds the step kernel's
-// queue use.
-bool pool_mode()
-{
-    const gv_config& c = L.cfg;
-    return c.driver == GV_DRIVER_BATCHED && c.trace_cap == 0 && c.capacity == 0 && !c.basket && !c.occupancy &&
-           !c.inner_steps && !c.graph_steps;
-}
-
 // Time a wavefront takes per launch once its input is used up (microseconds):
 // longer, and wavefronts that have emptied their pools wait for the others;
 // shorter, and launches and their read-backs (~25 us) weigh more (1000 x 10 GeV
@@ -1160,6 +1168,7 @@ int run_pool_window(size_t b, size_t e, uint64_t seed, const Tuning& tu, BulkRat
         if (launches > bound) return fail(GV_E_STATE, "step loop did not terminate within its launch bound");
     }
     if (in_tail) L.stats.tail_steps += (int64_t)steps - tail_steps0;
+    L.peak = std::max(L.peak, peak);
     return GV_OK;
 }
 
@@ -1275,20 +1284,38 @@ int reset_run_buffers(int64_t n_events)
 // against 90 with four); coordinate search over inner steps, then basket, then
 // occupancy, from the defaults; a candidate replaces the incumbent only if it
 // is at least 3 % faster.  The choice is cached per precision, queue order and
-// batch-size class; the trials' deposits and counters are discarded.
+// batch-size class; the trials' deposits and counters are discarded.  With the
+// pool driver a sample whose population never fills the GPU ends the search: the
+// defaults stand, as `tuned` says, until a batch of the class proves to be another
+// kind (revise_tuning).
+using TuneKey = std::tuple<int, int, int>;
+template <class P> TuneKey tune_key()
+{
+    int lg = 0;
+    while ((int64_t(1) << (lg + 1)) <= L.n_prim) ++lg;
+    return TuneKey((int)P::kMixed, (int)L.cfg.queue_order, lg);
+}
+
+// A batch that peaked at four times the tail threshold is not of the kind that the
+// entry's sample was: half of it would have passed the threshold.  An entry without
+// a measurement is dropped then, and the next batch of its class tuned.
+template <class P> void revise_tuning(const Tuning& tu)
+{
+    const auto it = L.tune_cache.find(tune_key<P>());
+    if (it != L.tune_cache.end() && !it->second.measured && L.peak / 4 >= tu.tail) L.tune_cache.erase(it);
+}
+
 template <class P> int tuned_choice(int64_t n_events, uint64_t seed, std::array<int, 3>& choice)
 {
     L.tuned = false;
     L.autotune_ms = 0.0;
     const bool free_knob = !L.cfg.basket || !L.cfg.occupancy || !L.cfg.inner_steps;
     if (!free_knob || L.n_prim < kTuneMinPrimaries) return GV_OK;
-    int lg = 0;
-    while ((int64_t(1) << (lg + 1)) <= L.n_prim) ++lg;
-    const auto key = std::make_tuple((int)P::kMixed, (int)L.cfg.queue_order, lg);
+    const TuneKey key = tune_key<P>();
     auto it = L.tune_cache.find(key);
     if (it != L.tune_cache.end()) {
-        choice = it->second;
-        L.tuned = true;
+        choice = it->second.choice;
+        L.tuned = it->second.measured;
         return GV_OK;
     }
     const double t0 = now_ms();
@@ -1296,6 +1323,7 @@ template <class P> int tuned_choice(int64_t n_events, uint64_t seed, std::array<
     while (ne < n_events && L.ev_start[ne] < 1024) ne = std::min(n_events, 2 * ne);
     const size_t cap = batch_cap<P>();
     const uint64_t tseed = seed ^ 0x6175746f74756e65ull;
+    bool bulk_ran = false;
     auto trial = [&](const std::array<int, 3>& c, double& rate) -> int {
         const Tuning tu = pick_tuning(c);
         int rc = ensure_status(cap, tu.block);
@@ -1307,6 +1335,7 @@ template <class P> int tuned_choice(int64_t n_events, uint64_t seed, std::array<
         BulkRate bulk;
         rc = pool_mode() ? run_pool_window<P>(L.ev_start[0], L.ev_start[ne], tseed, tu, &bulk)
                          : run_batched_window<P>(L.ev_start[0], L.ev_start[ne], tseed, tu);
+        bulk_ran |= rc == GV_E_CAPACITY || bulk.steps > 0;
         if (rc == GV_E_CAPACITY) {
             rate = 0.0;
             return GV_OK;
@@ -1327,11 +1356,13 @@ template <class P> int tuned_choice(int64_t n_events, uint64_t seed, std::array<
     double best_rate = 0.0;
     int rc = trial(best, best_rate);
     if (rc) return rc;
+    // a sample that stays in the pool kernel has no use for the knobs
+    const bool measured = !pool_mode() || bulk_ran;
     static const int kCand[3][8] = {{64, 128, 256, 512, 1024, 2048, 4096, 0}, {1, 2, 3, 4, 6, 8, 0, 0},
                                     {1, 2, 4, 8, 0, 0, 0, 0}};
     const int fixed[3] = {L.cfg.basket, L.cfg.occupancy, L.cfg.inner_steps};
     for (int knob : {2, 0, 1}) {
-        if (fixed[knob]) continue;
+        if (fixed[knob] || !measured) continue;
         const std::array<int, 3> base = best;
         for (int v : kCand[knob]) {
             if (v == 0 || v == base[knob]) continue;
@@ -1348,8 +1379,8 @@ template <class P> int tuned_choice(int64_t n_events, uint64_t seed, std::array<
         }
     }
     choice = best;
-    L.tune_cache[key] = best;
-    L.tuned = true;
+    L.tune_cache[key] = {best, measured};
+    L.tuned = measured;
     L.autotune_ms = now_ms() - t0;
     // discard the trials' results; the transport proper starts clean
     rc = reset_run_buffers(n_events);
@@ -1385,6 +1416,7 @@ template <class P> int transport_batched(int64_t n_events, uint64_t seed)
     int rc = tuned_choice<P>(n_events, seed, choice);
     if (rc) return rc;
     const Tuning tu = pick_tuning(choice);
+    L.peak = 0;
     rc = ensure_status(cap, tu.block);
     if (rc) return rc;
     L.stats.basket = tu.block * tu.chunks;
@@ -1416,6 +1448,7 @@ template <class P> int transport_batched(int64_t n_events, uint64_t seed)
         if (rc) return rc;
         e0 = e1;
     }
+    revise_tuning<P>(tu);
     return GV_OK;
 }
 

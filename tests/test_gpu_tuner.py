@@ -1,0 +1,38 @@
+"""What the autotuner of the knobs left at 0 compares and keeps (batches of at
+least 4096 primaries): statements about the choice and its counters, no timing."""
+import numpy as np
+import pytest
+
+import gv_inputs
+
+pytestmark = pytest.mark.gpu
+
+
+def _low(n, seed=5):
+    """Showers that stay below the population the step kernel takes."""
+    return gv_inputs.mixed_beam(n, seed, 30.0, 300.0)
+
+
+def test_batch_that_never_fills_the_gpu_keeps_the_defaults():
+    """Between the thresholds that baskets of 64 and of 256 would have (32,768 and
+    131,072 tracks on 256 CUs), no candidate has step-kernel work to be timed by:
+    the defaults stand and the pool kernel keeps the batch.  A batch of the same
+    size that does fill the GPU afterwards is tuned."""
+    import paper_2005_00949_amd as gv
+    eng = gv.Engine(gv_inputs.slab_calorimeter(50, (0.0, 4.0, 0.0)), max_steps_per_track=2000)
+    for k in range(2):
+        eng.transport(_low(6000), k)
+        s = eng.stats()
+        assert (s["basket"], s["occupancy"], s["inner_steps"]) == (256, 3, 4), s["basket"]
+        assert s["tuned"] == 0 and s["graph_replays"] == 0
+    assert s["autotune_ms"] == 0.0          # and the search is not repeated
+    high = gv_inputs.beam(4200, 11, 1.0e4)
+    eng.transport(high, 3)
+    assert eng.stats()["graph_replays"] > 0
+    eng.transport(high, 4)
+    s = eng.stats()
+    assert s["tuned"] == 1 and s["autotune_ms"] > 0.0
+    eng.transport(high, 5)
+    s = eng.stats()
+    assert s["tuned"] == 1 and s["autotune_ms"] == 0.0
+    eng.close()
