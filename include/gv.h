@@ -172,11 +172,12 @@ typedef struct {
     int32_t inner_steps;            /* max steps a track takes in registers per launch, 0 = tuned.
                                        Knobs left at 0 are chosen by the autotuner for batches
                                        of >= 4096 primaries (trial transports of a sample of
-                                       the batch, choice cached per precision, order and batch
-                                       size class), otherwise they take the defaults
-                                       256 / 3 / 4.  With all knobs and graph_steps and
-                                       capacity at 0 and no trace, populations too small to
-                                       fill the GPU run in the pool kernel, which has none */
+                                       the batch, choice cached per precision, order, field
+                                       method, kind of driver and batch size class), otherwise
+                                       they take the defaults 256 / 3 / 4.  With all knobs
+                                       and graph_steps and capacity at 0 and no trace,
+                                       populations too small to fill the GPU run in the pool
+                                       kernel, which has none */
     int32_t graph_steps;            /* step launches per captured graph, 0 = default */
     int32_t field_method;           /* GV_FIELD_HELIX, GV_FIELD_RK4 or GV_FIELD_RK45 */
     int32_t edep_on_device;         /* edep_out of gv_transport is a device pointer */

@@ -212,14 +212,14 @@ struct Lib {
     bool kept = false;   // device memory of a previous context is still here
     size_t staged_b = 0, staged_e = 0;   // window whose queue slots are on the device
     bool staged_one_queue = false;       // ... laid out for one mixed pool (plain) or per type
-    // autotuner choices, per (precision, queue order, log2 of the batch size);
-    // cleared by gv_init.  measured: false if the sample had no step-kernel work
+    // autotuner choices, per (precision, queue order, field method, whether the
+    // pool kernel takes part, log2 of the batch size); cleared by gv_init.  measured: false if the sample had no step-kernel work
     // to time, and the defaults stand
     struct TuneEntry {
         std::array<int, 3> choice;
         bool measured;
     };
-    std::map<std::tuple<int, int, int>, TuneEntry> tune_cache;
+    std::map<std::tuple<int, int, int, int, int>, TuneEntry> tune_cache;
     uint32_t peak = 0;   // largest population the pool driver has seen in this transport
     double autotune_ms = 0.0;
     bool tuned = false;
@@ -1283,17 +1283,18 @@ int reset_run_buffers(int64_t n_events)
 // workgroups per CU on some runs, 111 ms for the shower phase of the c4 batch
 // against 90 with four); coordinate search over inner steps, then basket, then
 // occupancy, from the defaults; a candidate replaces the incumbent only if it
-// is at least 3 % faster.  The choice is cached per precision, queue order and
+// is at least 3 % faster.  The choice is cached per precision, queue order, field
+// method (another kernel each), driver (pool or step kernel in the tail) and
 // batch-size class; the trials' deposits and counters are discarded.  With the
 // pool driver a sample whose population never fills the GPU ends the search: the
 // defaults stand, as `tuned` says, until a batch of the class proves to be another
 // kind (revise_tuning).
-using TuneKey = std::tuple<int, int, int>;
+using TuneKey = std::tuple<int, int, int, int, int>;
 template <class P> TuneKey tune_key()
 {
     int lg = 0;
     while ((int64_t(1) << (lg + 1)) <= L.n_prim) ++lg;
-    return TuneKey((int)P::kMixed, (int)L.cfg.queue_order, lg);
+    return TuneKey((int)P::kMixed, (int)L.cfg.queue_order, (int)L.cfg.field_method, (int)pool_mode(), lg);
 }
 
 // A batch that peaked at four times the tail threshold is not of the kind that the

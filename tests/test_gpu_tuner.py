@@ -36,3 +36,26 @@ def test_batch_that_never_fills_the_gpu_keeps_the_defaults():
     s = eng.stats()
     assert s["tuned"] == 1 and s["autotune_ms"] == 0.0
     eng.close()
+
+
+def test_choice_is_made_anew_for_another_kernel():
+    """A choice timed on the helix's step kernel with the pool kernel beside it says
+    nothing about the integrators' kernels, nor about a transport that a trace or a
+    capacity keeps in the step kernel from end to end."""
+    import paper_2005_00949_amd as gv
+    eng = gv.Engine(gv_inputs.slab_calorimeter(20, (0.0, 4.0, 0.0)), max_steps_per_track=2000)
+    prim = gv_inputs.beam(4096, 11, 3.0e3)
+    for change in ({}, dict(field_method=gv.FIELD_RK45), dict(trace_cap=1)):
+        eng.configure(**change)
+        eng.transport(prim, 1)
+        s = eng.stats()
+        assert s["tuned"] == 1 and s["autotune_ms"] > 0.0, change
+        eng.transport(prim, 2)
+        s = eng.stats()
+        assert s["tuned"] == 1 and s["autotune_ms"] == 0.0, change
+    # a capacity has the step kernel from end to end too: the trace's choice serves
+    eng.configure(trace_cap=0, capacity=1 << 24)
+    eng.transport(prim, 1)
+    s = eng.stats()
+    assert s["tuned"] == 1 and s["autotune_ms"] == 0.0
+    eng.close()
