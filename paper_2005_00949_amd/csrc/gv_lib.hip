@@ -1075,10 +1075,34 @@ template <class P> void launch_pool_helper(int parity, hipStream_t s)
 // pairs.
 // A trial of the autotuner takes the bulk replays alone (its knobs have no part
 // in the pool kernel): their time and steps go to `bulk_only`, and the window is
-// left once its population has fallen below the tail threshold.
+// left once its population has fallen below the tail threshold, or the trial
+// behind the incumbent.
 struct BulkRate {
     double ms = 0.0;
     unsigned long long steps = 0;
+    std::vector<std::pair<unsigned long long, double>> curve;   // steps and ms after each replay
+    const BulkRate* incumbent = nullptr;
+    // A candidate replaces the incumbent if it is 3 % faster.  One that has taken
+    // 15 % longer for the same steps, and half a millisecond (a graph's first
+    // launch), does not get there: trials are of the same histories, so the same
+    // steps are much the same work, from the end of the incumbent's first replay
+    // on.  (Half of the c4 batch, sixteen trials: 1,126 -> @@ ms.)
+    bool behind() const
+    {
+        if (!incumbent || incumbent->curve.empty()) return false;
+        if ((double)steps < 0.9 * (double)incumbent->curve.front().first) return false;
+        double s0 = 0.0, t0 = 0.0;
+        for (const auto& [s, t1] : incumbent->curve) {
+            const double s1 = (double)s;
+            if ((double)steps <= s1 && s1 > s0) {
+                t0 += (t1 - t0) * ((double)steps - s0) / (s1 - s0);
+                break;
+            }
+            s0 = s1;
+            t0 = t1;
+        }
+        return ms > 1.15 * t0 + 0.5;
+    }
 };
 
 template <class P>
@@ -1158,6 +1182,8 @@ int run_pool_window(size_t b, size_t e, uint64_t seed, const Tuning& tu, BulkRat
         if (bulk && bulk_only) {
             bulk_only->ms += ms;
             bulk_only->steps += m.steps - steps;
+            bulk_only->curve.emplace_back(bulk_only->steps, bulk_only->ms);
+            if (bulk_only->behind()) return GV_OK;
         }
         steps = m.steps;
         n_gamma = m.count[0];
@@ -1325,6 +1351,7 @@ template <class P> int tuned_choice(int64_t n_events, uint64_t seed, std::array<
     const size_t cap = batch_cap<P>();
     const uint64_t tseed = seed ^ 0x6175746f74756e65ull;
     bool bulk_ran = false;
+    BulkRate bulk, incumbent;
     auto trial = [&](const std::array<int, 3>& c, double& rate) -> int {
         const Tuning tu = pick_tuning(c);
         int rc = ensure_status(cap, tu.block);
@@ -1333,7 +1360,8 @@ template <class P> int tuned_choice(int64_t n_events, uint64_t seed, std::array<
         if (rc) return rc;
         L.stats.iterations = 0;
         const double k0 = L.stats.kernel_ms;
-        BulkRate bulk;
+        bulk = BulkRate{};
+        bulk.incumbent = &incumbent;
         rc = pool_mode() ? run_pool_window<P>(L.ev_start[0], L.ev_start[ne], tseed, tu, &bulk)
                          : run_batched_window<P>(L.ev_start[0], L.ev_start[ne], tseed, tu);
         bulk_ran |= rc == GV_E_CAPACITY || bulk.steps > 0;
@@ -1346,7 +1374,7 @@ template <class P> int tuned_choice(int64_t n_events, uint64_t seed, std::array<
         HIPCHK(hipMemcpyAsync(cnt, L.counters.p, sizeof(cnt), hipMemcpyDeviceToHost, stream()));
         HIPCHK(hipStreamSynchronize(stream()));
         const double ms = L.stats.kernel_ms - k0;
-        if (pool_mode()) rate = bulk.ms > 0.0 ? (double)bulk.steps / bulk.ms : 0.0;
+        if (pool_mode()) rate = bulk.ms > 0.0 && !bulk.behind() ? (double)bulk.steps / bulk.ms : 0.0;
         else rate = ms > 0.0 ? (double)(cnt[kCSteps] + cnt[kCSteps + 1] + cnt[kCSteps + 2]) / ms : 0.0;
         if (L.progress)
             std::fprintf(stderr, "[gv] autotune basket %d occupancy %d inner %d: %.4g steps/ms\n", c[0], c[1], c[2],
@@ -1357,6 +1385,7 @@ template <class P> int tuned_choice(int64_t n_events, uint64_t seed, std::array<
     double best_rate = 0.0;
     int rc = trial(best, best_rate);
     if (rc) return rc;
+    incumbent = bulk;
     // a sample that stays in the pool kernel has no use for the knobs
     const bool measured = !pool_mode() || bulk_ran;
     static const int kCand[3][8] = {{64, 128, 256, 512, 1024, 2048, 4096, 0}, {1, 2, 3, 4, 6, 8, 0, 0},
@@ -1376,6 +1405,7 @@ template <class P> int tuned_choice(int64_t n_events, uint64_t seed, std::array<
             if (r > 1.03 * best_rate) {
                 best_rate = r;
                 best = c;
+                incumbent = bulk;
             }
         }
     }

@@ -59,3 +59,21 @@ def test_choice_is_made_anew_for_another_kernel():
     s = eng.stats()
     assert s["tuned"] == 1 and s["autotune_ms"] == 0.0
     eng.close()
+
+
+def test_trials_that_fall_behind_end_early():
+    """Sixteen trials of half a batch, run to the end, take at least eight times the
+    kernel time of the batch (no knobs are much better than the ones it runs with);
+    trials that end once they have fallen behind take less."""
+    import paper_2005_00949_amd as gv
+    eng = gv.Engine(gv_inputs.slab_calorimeter(50), max_steps_per_track=2000)
+    prim = gv_inputs.beam(4200, 11, 1.0e4)
+    eng.transport(prim, 1)
+    tune = eng.stats()["autotune_ms"]
+    kernel = []
+    for k in range(3):
+        eng.transport(prim, 2 + k)
+        kernel.append(eng.stats()["kernel_ms"])
+    print(f"\nautotune {tune:.0f} ms, batch {min(kernel):.1f} ms")
+    assert 0.0 < tune < 8.0 * min(kernel)
+    eng.close()
