@@ -1086,7 +1086,7 @@ struct BulkRate {
     // 15 % longer for the same steps, and half a millisecond (a graph's first
     // launch), does not get there: trials are of the same histories, so the same
     // steps are much the same work, from the end of the incumbent's first replay
-    // on.  (Half of the c4 batch, sixteen trials: 1,126 -> @@ ms.)
+    // on.  (Half of the c4 batch, sixteen trials: 1,126 -> 470 to 540 ms.)
     bool behind() const
     {
         if (!incumbent || incumbent->curve.empty()) return false;
