@@ -936,13 +936,15 @@ __device__ __forceinline__ void make_interaction(const Ctx<P>& c, const Sinks& S
 // events 47.5 -> 41 ms.  Mixed precision, whose samplers are short, gains 2 %
 // there and loses 10 % on the barrel (lanes that end early), and samples in the
 // loop.
-template <class P, bool PHOTON, int BLOCK, bool STABLE, bool INTEG, bool PARK = false, class R = typename P::R>
+// VAC: the vacuum forms are compiled in (see k_step_batched).
+template <class P, bool PHOTON, int BLOCK, bool STABLE, bool INTEG, bool PARK, bool VAC, class R = typename P::R>
 __device__ __forceinline__ void process_chunk(uint64_t seed, const int ty, uint32_t chunk, uint32_t base,
                                               uint32_t n_t, uint32_t epoch, int inner, ScanShared<BLOCK>& sh,
                                               DepCache& dc, unsigned* cnt_lds, uint32_t& steps_here,
                                               uint32_t& loads, uint32_t& stores, uint32_t n_chunks, RkSum& rks,
                                               unsigned long long* lane_slots_lds, int min_lanes)
 {
+    static_assert(!VAC || (!INTEG && !PARK), "the vacuum forms are for the helix");
     constexpr bool kDefer = !P::kMixed;
     const BatchArgs<P>& A = step_args<P>();
     const uint32_t slot = base + threadIdx.x;
@@ -968,7 +970,36 @@ __device__ __forceinline__ void process_chunk(uint64_t seed, const int ty, uint3
             if (iters > 0 && __popcll(__ballot(1)) < min_lanes) break;
             const BatchArgs<P>& A = step_args<P>();
             const Ctx<P> c = stage_ctx<P>(A.tv, seed);
-            if (PARK && !PHOTON) {
+            const bool acc_empty = (acc.e == 0.0) & (acc.x == 0ull);
+            if (VAC && !PHOTON && __all((t.vol == 0) & acc_empty)) {
+                // A step that leaves its track alive in vacuum changes nothing
+                // but the track (no deposit, process, secondary, counter or
+                // ledger entry; the deposit accumulator stays empty, so its
+                // volume does not matter), so such steps repeat with only the
+                // step count and the trace; the step that ends otherwise takes
+                // the bookkeeping below like any other.
+                const Ctx<P> cv{seed, &c_geom, &c_phys, A.tv};
+                const bool traced = A.S.trace != nullptr;
+                const WorldRun<P> run = world_run(cv, t);
+                for (;;) {
+                    step_world(cv, run, t, o);
+                    steps_here += o.did_step;
+                    iters += 1;
+                    if (o.status != kAlive || t.vol != 0 || iters >= inner) break;
+                    if (traced && o.did_step) trace_step(A.S, t, o.vol_pre, t, o, t.nstep - 1u);
+                }
+            } else if (VAC && !PHOTON && __all((vol_material(c_geom, t.vol) < 0) & acc_empty)) {
+                const Ctx<P> cv{seed, &c_geom, &c_phys, A.tv};
+                const bool traced = A.S.trace != nullptr;
+                for (;;) {
+                    step_track<P, false, true>(cv, t, o);
+                    steps_here += o.did_step;
+                    iters += 1;
+                    if (o.status != kAlive || iters >= inner) break;
+                    if (t.vol != o.vol_pre && vol_material(c_geom, t.vol) >= 0) break;
+                    if (traced && o.did_step) trace_step(A.S, t, o.vol_pre, t, o, t.nstep - 1u);
+                }
+            } else if (PARK && !PHOTON) {
                 Limits<R> L;
                 Geo G;
                 Prop<R> pr;
@@ -1078,8 +1109,15 @@ __device__ __forceinline__ void process_chunk(uint64_t seed, const int ty, uint3
 // in a field and so has the helix variant's register budget.  That budget is
 // four wavefronts per SIMD in mixed precision (128 VGPRs; 7 % faster than three)
 // and two in FP64 (256; one without it), at the price of a few spills.
-template <class P, int BLOCK, bool STABLE, bool INTEG, bool PARK = false>
-__global__ void __launch_bounds__(BLOCK, (!INTEG && sizeof(typename P::R) == sizeof(float)) ? 4 : !INTEG ? 2 : 1)
+// VAC (helix in a uniform field): a wavefront whose charged tracks are all in
+// volumes without material steps them in the vacuum form of the step in a loop of
+// its own.  Populations below the tail threshold have it: there loopers circle in vacuum for up to max_steps_per_track steps, and a launch lasts as long
+// as its slowest wavefront (2,000 loopers of 20,000 steps: 64 -> 32 ms mixed,
+// 69 -> 43 ms FP64; 1,000 c4 events, with one or two loopers beside tracks in
+// material at the end: 49 -> 38 ms).  Larger populations do without: its code
+// and registers cost them more than the few such wavefronts gain.
+template <class P, int BLOCK, bool STABLE, bool INTEG, bool PARK = false, bool VAC = false>
+__global__ void __launch_bounds__(BLOCK, INTEG ? 1 : P::kMixed ? (VAC ? 3 : 4) : (VAC ? 1 : 2))
 k_step_batched(BatchArgs<P>)
 {
     const BatchArgs<P>& A = step_args<P>();
@@ -1131,13 +1169,13 @@ k_step_batched(BatchArgs<P>)
         const uint32_t last = min(first + (uint32_t)A.basket_chunks, n_chunks);
         for (uint32_t chunk = first; chunk < last; ++chunk) {
             if (chunk < c0) {
-                process_chunk<P, true, BLOCK, STABLE, INTEG, PARK>(seed, kGamma, chunk, chunk * BLOCK, n0, epoch, inner,
+                process_chunk<P, true, BLOCK, STABLE, INTEG, PARK, VAC>(seed, kGamma, chunk, chunk * BLOCK, n0, epoch, inner,
                                                                    sh, dc, cnt_lds, steps_g, loads, stores, n_chunks,
                                                                    rks, &rk_lds[3], min_lanes);
             } else {
                 const bool ele = chunk < c0 + c1;
                 uint32_t n = 0;
-                process_chunk<P, false, BLOCK, STABLE, INTEG, PARK>(
+                process_chunk<P, false, BLOCK, STABLE, INTEG, PARK, VAC>(
                     seed, ele ? kElectron : kPositron, chunk, (ele ? chunk - c0 : chunk - c0 - c1) * BLOCK,
                     ele ? n1 : n2, epoch, inner, sh, dc, cnt_lds, n, loads, stores, n_chunks, rks, &rk_lds[3], min_lanes);
                 steps_e += ele ? n : 0u;

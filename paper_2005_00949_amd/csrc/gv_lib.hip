@@ -144,6 +144,11 @@ struct GraphKey {
     }
 };
 
+// The step kernel's graphs: bulk (populations that fill the GPU, and any where the
+// step has no vacuum form), rising (below the tail threshold, before the peak) and
+// tail (below it and past the peak: more launches per replay, the vacuum helper).
+enum : int { kGraphBulk = 0, kGraphRising = 1, kGraphTail = 2, kNGraph = 3 };
+
 struct Lib {
     bool ready = false;
     bool busy = false;
@@ -188,10 +193,8 @@ struct Lib {
     DBuf<uint32_t> prim_slot;
     Ctrl* h_ctrl = nullptr;  // pinned
     CtrlMirror* h_mirror = nullptr;  // pinned, written by the pool kernel
-    hipGraphExec_t gexec = nullptr;      // bulk: full grid, bulk inner steps
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t gexec_tail = nullptr; // tail: small grid, tail inner steps
-    hipGraph_t graph_tail = nullptr;
+    hipGraph_t graph[kNGraph] = {};
+    hipGraphExec_t gexec[kNGraph] = {};
     GraphKey gkey;
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     gv_stats_t stats{};
@@ -260,14 +263,12 @@ hipStream_t stream() { return L.cfg.hip_stream ? (hipStream_t)L.cfg.hip_stream :
 
 void drop_graph()
 {
-    if (L.gexec) (void)hipGraphExecDestroy(L.gexec);
-    if (L.graph) (void)hipGraphDestroy(L.graph);
-    if (L.gexec_tail) (void)hipGraphExecDestroy(L.gexec_tail);
-    if (L.graph_tail) (void)hipGraphDestroy(L.graph_tail);
-    L.gexec = nullptr;
-    L.graph = nullptr;
-    L.gexec_tail = nullptr;
-    L.graph_tail = nullptr;
+    for (int k = 0; k < kNGraph; ++k) {
+        if (L.gexec[k]) (void)hipGraphExecDestroy(L.gexec[k]);
+        if (L.graph[k]) (void)hipGraphDestroy(L.graph[k]);
+        L.gexec[k] = nullptr;
+        L.graph[k] = nullptr;
+    }
     L.gkey = GraphKey{};
 }
 
@@ -762,26 +763,36 @@ int ingest(size_t b, size_t e, Soa<P> q[3], uint32_t counts[3], size_t cap, bool
     return GV_OK;
 }
 
-template <class P, int BLOCK, bool INTEG> void launch_step(const BatchArgs<P>& A, int grid, bool stable, hipStream_t s)
+template <class P, int BLOCK, bool INTEG, bool VAC>
+void launch_step(const BatchArgs<P>& A, int grid, bool stable, hipStream_t s)
 {
-    if (stable) k_step_batched<P, BLOCK, true, INTEG><<<grid, BLOCK, 0, s>>>(A);
-    else k_step_batched<P, BLOCK, false, INTEG><<<grid, BLOCK, 0, s>>>(A);
+    if (stable) k_step_batched<P, BLOCK, true, INTEG, false, VAC><<<grid, BLOCK, 0, s>>>(A);
+    else k_step_batched<P, BLOCK, false, INTEG, false, VAC><<<grid, BLOCK, 0, s>>>(A);
 }
 
-template <class P, bool INTEG>
+template <class P, bool INTEG, bool VAC>
 void launch_step_block(int block, const BatchArgs<P>& A, int grid, bool stable, hipStream_t s)
 {
     switch (block) {
-    case 64: launch_step<P, 64, INTEG>(A, grid, stable, s); break;
-    case 128: launch_step<P, 128, INTEG>(A, grid, stable, s); break;
-    default: launch_step<P, 256, INTEG>(A, grid, stable, s); break;
+    case 64: launch_step<P, 64, INTEG, VAC>(A, grid, stable, s); break;
+    case 128: launch_step<P, 128, INTEG, VAC>(A, grid, stable, s); break;
+    default: launch_step<P, 256, INTEG, VAC>(A, grid, stable, s); break;
     }
 }
 
-template <class P> void launch_step_dispatch(int block, const BatchArgs<P>& A, int grid, bool stable, hipStream_t s)
+// whether tracks circle in vacuum in a form of their own: helix in a uniform field
+bool vacuum_forms()
 {
-    if (L.cfg.field_method != GV_FIELD_HELIX) launch_step_block<P, true>(block, A, grid, stable, s);
-    else launch_step_block<P, false>(block, A, grid, stable, s);
+    return L.cfg.field_method == GV_FIELD_HELIX && L.geom.field_map == kMapUniform && L.geom.Bmag > 0.0;
+}
+
+// vac: the step kernel with the vacuum forms (vacuum_forms)
+template <class P>
+void launch_step_dispatch(int block, const BatchArgs<P>& A, int grid, bool stable, hipStream_t s, bool vac)
+{
+    if (L.cfg.field_method != GV_FIELD_HELIX) launch_step_block<P, true, false>(block, A, grid, stable, s);
+    else if (vac) launch_step_block<P, false, true>(block, A, grid, stable, s);
+    else launch_step_block<P, false, false>(block, A, grid, stable, s);
 }
 
 // RK45 with arrival-order queues runs its integrations through the
@@ -847,13 +858,16 @@ constexpr int kVacHelperSteps = 4096;
 // the pool driver, which launches it only for loopers, gives it a block per CU)
 constexpr int kVacHelperGraphGrid = 64;
 
-// capture K launches alternating parity (K even: a replay ends where it began);
-// tail: the tail graph, with the vacuum helper before each step launch and,
-// for RK45 with arrival order, integration inside the step only
-template <class P>
-int capture(const Tuning& tu, int grid, int K, int inner_bulk, int inner_tail, bool tail, hipGraph_t* g,
-            hipGraphExec_t* ge)
+// capture one of the graphs: K launches alternating parity (K even: a replay ends
+// where it began); the tail graph with the vacuum helper before each step launch
+// and, for RK45 with arrival order, integration inside the step only
+template <class P> int capture(const Tuning& tu, int which)
 {
+    if (L.graph[which]) (void)hipGraphDestroy(L.graph[which]);   // (left by a capture that failed)
+    L.graph[which] = nullptr;
+    const bool tail = which == kGraphTail;
+    const int grid = tail ? tu.tail_grid : tu.occupancy * L.n_cu, K = tail ? tu.tail_K : tu.K;
+    const int inner_bulk = tail ? tu.inner_tail : tu.inner_bulk, inner_tail = tu.inner_tail;
     QueueMem<P>& Q = batch_queues<P>();
     hipStream_t s = stream();
     BatchArgs<P> A[2];
@@ -895,18 +909,16 @@ int capture(const Tuning& tu, int grid, int K, int inner_bulk, int inner_tail, b
                 k_vacuum_helper<P, kHelperHelix><<<kVacHelperGraphGrid, kVacHelperBlock, 0, s>>>(A[k & 1], kVacHelperSteps);
         }
         if (rkq) launch_rk_queue_step<P>(tu.block, A[k & 1], grid, s, tail);
-        else launch_step_dispatch<P>(tu.block, A[k & 1], grid, stable, s);
+        else launch_step_dispatch<P>(tu.block, A[k & 1], grid, stable, s, which != kGraphBulk && vacuum_forms());
     }
-    hipError_t ce = hipStreamEndCapture(s, g);
+    hipError_t ce = hipStreamEndCapture(s, &L.graph[which]);
     if (ce != hipSuccess) return fail(GV_E_HIP, std::string("graph capture: ") + hipGetErrorString(ce));
-    HIPCHK(hipGraphInstantiate(ge, *g, nullptr, nullptr, 0));
+    HIPCHK(hipGraphInstantiate(&L.gexec[which], L.graph[which], nullptr, nullptr, 0));
     return GV_OK;
 }
 
-// the step kernel's graphs for the current options, captured if they are not
-// there; with_tail: the tail graph too (the pool driver replays the bulk graph
-// alone, and a tail graph is another 64 step and 64 helper launches to capture)
-template <class P> int ensure_graphs(const Tuning& tu, bool with_tail)
+// one of the step kernel's graphs for the current options, captured if it is not there
+template <class P> int ensure_graph(const Tuning& tu, int which)
 {
     QueueMem<P>& Q = batch_queues<P>();
     GraphKey key;
@@ -929,19 +941,8 @@ template <class P> int ensure_graphs(const Tuning& tu, bool with_tail)
     key.tail_grid = tu.tail_grid;
     key.tail_K = tu.tail_K;
     if (!(L.gkey == key)) drop_graph();
-    if (!L.gexec) {
-        int rc = capture<P>(tu, tu.occupancy * L.n_cu, tu.K, tu.inner_bulk, tu.inner_tail, false, &L.graph, &L.gexec);
-        if (rc) return rc;
-    }
-    // the vacuum helper steps the last loopers of the tail replays (with the
-    // looper forms of the helix in a uniform field, else the general step)
-    if (with_tail && !L.gexec_tail) {
-        int rc = capture<P>(tu, tu.tail_grid, tu.tail_K, tu.inner_tail, tu.inner_tail, true, &L.graph_tail,
-                            &L.gexec_tail);
-        if (rc) return rc;
-    }
     L.gkey = key;
-    return GV_OK;
+    return L.gexec[which] ? GV_OK : capture<P>(tu, which);
 }
 
 // batched transport of one event window; returns GV_E_CAPACITY on overflow
@@ -953,8 +954,6 @@ template <class P> int run_batched_window(size_t b, size_t e, uint64_t seed, con
     int rc = ingest<P>(b, e, Q.q[0], counts, Q.cap, false);
     if (rc) return rc;
     rc = upload_ctrl(counts, seed);
-    if (rc) return rc;
-    rc = ensure_graphs<P>(tu, true);
     if (rc) return rc;
     hipStream_t s = stream();
     uint32_t population = counts[0] + counts[1] + counts[2];
@@ -977,8 +976,11 @@ template <class P> int run_batched_window(size_t b, size_t e, uint64_t seed, con
             L.tail_steps0 += (int64_t)(c3[0] + c3[1] + c3[2]);
             in_tail = true;
         }
+        const int which = tail ? kGraphTail : population < tu.tail && vacuum_forms() ? kGraphRising : kGraphBulk;
+        rc = ensure_graph<P>(tu, which);
+        if (rc) return rc;
         HIPCHK(hipEventRecord(L.ev0, s));
-        HIPCHK(hipGraphLaunch(tail ? L.gexec_tail : L.gexec, s));
+        HIPCHK(hipGraphLaunch(L.gexec[which], s));
         HIPCHK(hipEventRecord(L.ev1, s));
         rc = read_ctrl();
         if (rc) return rc;
@@ -1134,12 +1136,12 @@ int run_pool_window(size_t b, size_t e, uint64_t seed, const Tuning& tu, BulkRat
         const bool helper = !bulk && n_vac == n && n_gamma == 0 && n <= (uint32_t)(L.n_cu * kVacHelperWaves);
         int K = 1;
         if (bulk) {   // captured, if need be, before the interval that counts as kernel time
-            rc = ensure_graphs<P>(tu, false);
+            rc = ensure_graph<P>(tu, kGraphBulk);
             if (rc) return rc;
         }
         HIPCHK(hipEventRecord(L.ev0, s));
         if (bulk) {
-            HIPCHK(hipGraphLaunch(L.gexec, s));
+            HIPCHK(hipGraphLaunch(L.gexec[kGraphBulk], s));
             K = tu.K;
         } else {
             if (helper) launch_pool_helper<P>(0, s);
