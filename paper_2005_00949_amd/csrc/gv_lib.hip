@@ -855,22 +855,13 @@ template <> QueueMem<PMix>& batch_queues<PMix>() { return L.qmix; }
 // vacuum steps per track and helper launch in the tail replays
 constexpr int kVacHelperSteps = 4096;
 // its blocks there, for 256 loopers (most of its launches find material and leave;
-// the pool driver, which launches it only for loopers, gives it a block per CU)
+// the pool driver, which launches it only for loopers, gives each a wavefront)
 constexpr int kVacHelperGraphGrid = 64;
 
-// capture one of the graphs: K launches alternating parity (K even: a replay ends
-// where it began); the tail graph with the vacuum helper before each step launch
-// and, for RK45 with arrival order, integration inside the step only
-template <class P> int capture(const Tuning& tu, int which)
+// the step kernel's arguments at either parity
+template <class P> void fill_step_args(const Tuning& tu, bool tail, BatchArgs<P> A[2])
 {
-    if (L.graph[which]) (void)hipGraphDestroy(L.graph[which]);   // (left by a capture that failed)
-    L.graph[which] = nullptr;
-    const bool tail = which == kGraphTail;
-    const int grid = tail ? tu.tail_grid : tu.occupancy * L.n_cu, K = tail ? tu.tail_K : tu.K;
-    const int inner_bulk = tail ? tu.inner_tail : tu.inner_bulk, inner_tail = tu.inner_tail;
     QueueMem<P>& Q = batch_queues<P>();
-    hipStream_t s = stream();
-    BatchArgs<P> A[2];
     for (int par = 0; par < 2; ++par) {
         for (int t = 0; t < 3; ++t) {
             A[par].in[t] = Q.q[par][t];
@@ -881,8 +872,8 @@ template <class P> int capture(const Tuning& tu, int which)
         A[par].cap = (uint32_t)Q.cap;
         A[par].parity = par;
         A[par].basket_chunks = tu.chunks;
-        A[par].inner_bulk = inner_bulk;
-        A[par].inner_tail = inner_tail;
+        A[par].inner_bulk = tail ? tu.inner_tail : tu.inner_bulk;
+        A[par].inner_tail = tu.inner_tail;
         A[par].tail_threshold = tu.tail;
         A[par].S = make_sinks();
         A[par].tv = tab_view<typename P::R>();
@@ -896,6 +887,20 @@ template <class P> int capture(const Tuning& tu, int which)
         A[par].regime = kRunAlways;
         A[par].min_lanes = tail ? 0 : kBulkMinLanes;
     }
+}
+
+// capture one of the graphs: K launches alternating parity (K even: a replay ends
+// where it began); the tail graph with the vacuum helper before each step launch
+// and, for RK45 with arrival order, integration inside the step only
+template <class P> int capture(const Tuning& tu, int which)
+{
+    if (L.graph[which]) (void)hipGraphDestroy(L.graph[which]);   // (left by a capture that failed)
+    L.graph[which] = nullptr;
+    const bool tail = which == kGraphTail;
+    const int grid = tail ? tu.tail_grid : tu.occupancy * L.n_cu, K = tail ? tu.tail_K : tu.K;
+    hipStream_t s = stream();
+    BatchArgs<P> A[2];
+    fill_step_args<P>(tu, tail, A);
     HIPCHK(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
     const bool stable = L.cfg.queue_order == GV_ORDER_STABLE;
     const bool rkq = rk_queue_mode();
@@ -1020,7 +1025,8 @@ template <class P> int run_batched_window(size_t b, size_t e, uint64_t seed, con
 
 // ---- the pool kernel's driver ----------------------------------------------
 
-// Time a wavefront takes per launch once its input is used up (microseconds):
+// Time a wavefront takes per launch, from its start, unless its input lasts longer
+// (microseconds):
 // longer, and wavefronts that have emptied their pools wait for the others;
 // shorter, and launches and their read-backs (~25 us) weigh more (1000 x 10 GeV
 // e-: 17.2 / 16.5 / 16.2 ms at 50 / 100 / 200 us; 100 x 50 GeV with RK45: 115 /
@@ -1032,6 +1038,16 @@ constexpr int kPoolInner = 8;
 constexpr int kPoolInnerInteg = 2;
 // vacuum steps per track and helper launch between two pool launches
 constexpr int kPoolHelperSteps = 65536;
+// Wavefronts per CU, each with a looper, up to which the helper takes a population of
+// loopers alone: as long as that is faster than a looper per lane in the step kernel.
+// One per SIMD with an integrator (1,000 / 2,048 RK45 loopers in the field map, 1,000
+// steps: 27 / 47 ms here, 39 ms there at any number), two in FP64 (2,048 / 3,000 /
+// 4,096 loopers of 20,000 steps, uniform field: 28 / 40 / 52 ms, and 44), four in mixed
+// precision (4,096: 23 and 33 ms; in the barrel 22 and 48).
+template <class P> int helper_waves()
+{
+    return L.cfg.field_method != GV_FIELD_HELIX ? 4 : P::kMixed ? 16 : 8;
+}
 
 template <class P> void launch_pool(int parity, int grid, hipStream_t s)
 {
@@ -1053,8 +1069,9 @@ template <class P> void launch_pool(int parity, int grid, hipStream_t s)
     else k_pool<P, false><<<grid, kPoolBlock, 0, s>>>(A);
 }
 
-template <class P> void launch_pool_helper(int parity, hipStream_t s)
+template <class P> void launch_pool_helper(int parity, uint32_t n, hipStream_t s)
 {
+    const unsigned grid = (n + kVacHelperWaves - 1) / kVacHelperWaves;
     QueueMem<P>& Q = batch_queues<P>();
     BatchArgs<P> A{};
     for (int t = 0; t < 3; ++t) A.in[t] = Q.q[parity][t];
@@ -1064,11 +1081,31 @@ template <class P> void launch_pool_helper(int parity, hipStream_t s)
     A.S = make_sinks();
     A.tv = tab_view<typename P::R>();
     if (L.cfg.field_method != GV_FIELD_HELIX)
-        k_vacuum_helper<P, kHelperInteg><<<L.n_cu, kVacHelperBlock, 0, s>>>(A, kVacHelperSteps);
+        k_vacuum_helper<P, kHelperInteg><<<grid, kVacHelperBlock, 0, s>>>(A, kVacHelperSteps);
     else if (L.geom.field_map == kMapUniform)
-        k_vacuum_helper<P, kHelperLooper><<<L.n_cu, kVacHelperBlock, 0, s>>>(A, kPoolHelperSteps);
+        k_vacuum_helper<P, kHelperLooper><<<grid, kVacHelperBlock, 0, s>>>(A, kPoolHelperSteps);
     else
-        k_vacuum_helper<P, kHelperHelix><<<L.n_cu, kVacHelperBlock, 0, s>>>(A, kPoolHelperSteps);
+        k_vacuum_helper<P, kHelperHelix><<<grid, kVacHelperBlock, 0, s>>>(A, kPoolHelperSteps);
+}
+
+// Loopers alone, more of them than the helper takes: the step kernel as the tail
+// graph launches it, up to 256 steps per track and launch, its wavefronts full.
+// The pool kernel would give each wavefront a few of them and stop them every
+// 100 us, that is 50 steps or, with an integrator, 5 (20,000 loopers of 20,000 steps
+// in a uniform field: 66 ms there, 36 ms here; 1,500 with RK45 in the field map, 3,000
+// steps: 426 and 110 ms).  An even number of launches, so that they end at parity
+// 0.
+constexpr int kLooperLaunches = 64;
+
+template <class P> int launch_loopers(const Tuning& tu, hipStream_t s)
+{
+    BatchArgs<P> A[2];
+    fill_step_args<P>(tu, true, A);
+    const bool stable = L.cfg.queue_order == GV_ORDER_STABLE;
+    for (int k = 0; k < kLooperLaunches; ++k)
+        launch_step_dispatch<P>(tu.block, A[k & 1], tu.tail_grid, stable, s, vacuum_forms());
+    HIPCHK(hipGetLastError());
+    return GV_OK;
 }
 
 // Batched transport of one event window with the pool kernel.  Populations
@@ -1133,7 +1170,10 @@ int run_pool_window(size_t b, size_t e, uint64_t seed, const Tuning& tu, BulkRat
             tail_steps0 = (int64_t)steps;
         }
         const bool bulk = n >= tu.tail;
-        const bool helper = !bulk && n_vac == n && n_gamma == 0 && n <= (uint32_t)(L.n_cu * kVacHelperWaves);
+        // (without a field a track in vacuum leaves it in its next step)
+        const bool loopers = !bulk && n_vac == n && n_gamma == 0 && (L.geom.Bmag > 0.0 || L.geom.field_map != kMapUniform);
+        const bool helper = loopers && n <= (uint32_t)(L.n_cu * helper_waves<P>());
+        const bool step_kernel = bulk || (loopers && !helper);
         int K = 1;
         if (bulk) {   // captured, if need be, before the interval that counts as kernel time
             rc = ensure_graph<P>(tu, kGraphBulk);
@@ -1143,8 +1183,12 @@ int run_pool_window(size_t b, size_t e, uint64_t seed, const Tuning& tu, BulkRat
         if (bulk) {
             HIPCHK(hipGraphLaunch(L.gexec[kGraphBulk], s));
             K = tu.K;
+        } else if (step_kernel) {
+            rc = launch_loopers<P>(tu, s);
+            if (rc) return rc;
+            K = kLooperLaunches;
         } else {
-            if (helper) launch_pool_helper<P>(0, s);
+            if (helper) launch_pool_helper<P>(0, n, s);
             const int grid = (int)std::min<uint32_t>((n + kPoolWaves - 1) / kPoolWaves, (uint32_t)grid_full);
             launch_pool<P>(0, grid, s);
             launch_pool<P>(1, std::min(16 * grid, grid_full), s);
@@ -1152,7 +1196,7 @@ int run_pool_window(size_t b, size_t e, uint64_t seed, const Tuning& tu, BulkRat
             HIPCHK(hipGetLastError());
         }
         HIPCHK(hipEventRecord(L.ev1, s));
-        if (bulk) {
+        if (step_kernel) {
             rc = read_ctrl();
             if (rc) return rc;
             unsigned long long c3[3];
@@ -1160,7 +1204,10 @@ int run_pool_window(size_t b, size_t e, uint64_t seed, const Tuning& tu, BulkRat
             HIPCHK(hipStreamSynchronize(s));
             CtrlMirror& m = *L.h_mirror;
             for (int t = 0; t < 3; ++t) m.count[t] = L.h_ctrl->count[0][t];
-            m.n_vac = 0;
+            // (the step kernel does not count them: what is left of loopers alone, without a
+            // photon, is taken for loopers; the helper looks for itself)
+            const uint32_t left = m.count[1] + m.count[2];
+            m.n_vac = loopers && m.count[0] == 0 && left <= n ? left : 0;
             m.overflow = L.h_ctrl->overflow;
             m.steps = c3[0] + c3[1] + c3[2];
         } else {
@@ -1179,7 +1226,7 @@ int run_pool_window(size_t b, size_t e, uint64_t seed, const Tuning& tu, BulkRat
         if (m.overflow) return GV_E_CAPACITY;
         if (L.progress)
             std::fprintf(stderr, "[gv] %s%s%s: %.3f ms, population %u/%u/%u, vacuum %u, steps %llu\n",
-                         bulk ? "bulk" : "pool", helper ? " helper" : "", tail ? " tail" : "", ms, m.count[0], m.count[1],
+                         bulk ? "bulk" : step_kernel ? "loopers" : "pool", helper ? " helper" : "", tail ? " tail" : "", ms, m.count[0], m.count[1],
                          m.count[2], m.n_vac, m.steps - steps);
         if (bulk && bulk_only) {
             bulk_only->ms += ms;

@@ -35,9 +35,10 @@
 // is the track alone (the tag says which process; the step count is advanced
 // after the interaction), so an interaction may be taken any time later.
 //
-// A pool belongs to one wavefront, so nothing in the loop waits for another;
-// and once its input is used up, a launch ends after `budget` ticks of the wall
-// clock (one stage more at most).
+// A pool belongs to one wavefront, so nothing in the loop waits for another.  A
+// wavefront whose input is used up begins no step `budget` ticks of the wall clock
+// after its own start, one stage apart; it makes the interactions that wait, which no
+// step follows, and leaves.
 #pragma once
 #include "gv_kernels.h"
 
@@ -91,7 +92,7 @@ template <class P> struct PoolArgs {
     CtrlMirror* mirror;    // what the host reads between launches
     uint32_t cap;
     int parity;
-    long long budget;      // wall-clock ticks after which a wavefront with no input left puts its tracks back
+    long long budget;      // wall-clock ticks from its start after which a wavefront with no input left puts its tracks back
     int inner;             // steps a track takes in registers per stage, at most
     Sinks S;
     TabView<typename P::R> tv;
@@ -644,10 +645,17 @@ __global__ void __launch_bounds__(kPoolBlock, PoolSize<P>::wgs(INTEG)) k_pool(Po
     __syncthreads();
 
     uint32_t next_chunk = wave;   // this wavefront's own chunk first, then whichever is left
-    bool drain = false;
+    bool drain = false, staged = false;
     const long long t0 = (long long)wall_clock64();
     for (;;) {
         int tag, n, slot;
+        // with no input left, the launch's share is done `budget` ticks after its
+        // start, and one stage at least: interactions that wait are taken (no step
+        // follows them), then the tracks go to the output queues, to be shared out
+        // evenly again.  By the clock and not by a count, because a stage may be one
+        // photon step or a hundred integration attempts, and the launch lasts as
+        // long as its slowest wavefront.
+        drain |= staged && next_chunk >= n_chunks && (long long)wall_clock64() - t0 >= pool_args<P>().budget;
         const bool input = !drain && next_chunk < n_chunks;
         const int what = pool_take(M, st, lane, drain, input, (int)chunk, tag, n, slot);
         if (what == kTakeNone) break;
@@ -681,14 +689,8 @@ __global__ void __launch_bounds__(kPoolBlock, PoolSize<P>::wgs(INTEG)) k_pool(Po
             }
             continue;
         }
-        // with no input left, the launch's share is done after `budget` ticks:
-        // interactions that wait are taken (none makes another), then the
-        // tracks go to the output queues, to be shared out evenly again.  By
-        // the clock and not by a count, because a stage may be one photon step
-        // or a hundred integration attempts, and the launch lasts as long as
-        // its slowest wavefront.
         const PoolArgs<P>& A = pool_args<P>();
-        drain |= !input && (long long)wall_clock64() - t0 >= A.budget;
+        staged = true;
         if (tag == kTagPhoton || tag == kTagCharged || tag == kTagVacuum) {
             Track<P> t;
             if (slot >= 0) pool_load(M, slot, t);

@@ -79,3 +79,36 @@ def test_step_kernel_steps_loopers_of_the_barrel(precision):
     geom, prim = loopers(300, gv_inputs.MAP_UNIFORM)
     cfg = dict(precision=getattr(gv, precision), max_steps_per_track=2_000)
     assert_same(run(gv, geom, prim, **cfg, **KNOBS), run(gv, geom, prim, **cfg))
+
+
+# (loopers, field map, method, looper cap): on either side of the numbers up to which
+# one wavefront per looper takes them, and many more
+MANY = {
+    "uniform 1100": (1100, None, 0, 4000),
+    "uniform 4200": (4200, None, 0, 20_000),
+    "barrel 2100": (2100, gv_inputs.MAP_UNIFORM, 0, 4000),
+    "map 1500": (1500, gv_inputs.MAP_SOLENOID, 0, 4000),
+    "map 5000": (5000, gv_inputs.MAP_SOLENOID, 0, 4000),
+    "rk45 1025": (1025, gv_inputs.MAP_SOLENOID, 2, 1000),
+    "rk45 uniform 1500": (1500, gv_inputs.MAP_UNIFORM, 2, 1000),
+    "rk4 uniform 1500": (1500, gv_inputs.MAP_UNIFORM, 1, 50),
+}
+
+
+@pytest.mark.parametrize("precision", ["PMIX", "P64"])
+@pytest.mark.parametrize("case", list(MANY))
+def test_many_loopers_without_knobs(case, precision):
+    """Loopers alone take no longer without knobs than in the step kernel: 1.25 leaves
+    the two launches of the pool kernel that find out (0.5 ms) and the noise of either
+    call a fifth each; the pool kernel alone took 1.4 times (4,200 in a uniform field)
+    to 4 times as long."""
+    import paper_2005_00949_amd as gv
+    n, field_map, method, cap = MANY[case]
+    geom, prim = loopers(n, field_map)
+    cfg = dict(precision=getattr(gv, precision), max_steps_per_track=cap, field_method=method)
+    a = run(gv, geom, prim, **cfg)
+    b = run(gv, geom, prim, **cfg, **KNOBS)
+    print(f"\n{case} {precision}: {a[4]:.2f} ms, with knobs {b[4]:.2f} ms")
+    assert_same(a, b)
+    if b[4] > 5.0:
+        assert a[4] < 1.25 * b[4]
