@@ -34,6 +34,7 @@ using namespace gv;
 namespace {
 
 thread_local std::string g_err;
+thread_local bool g_oom = false;   // the last failed HIP call found no device memory
 
 int fail(int code, const std::string& msg)
 {
@@ -44,7 +45,10 @@ int fail(int code, const std::string& msg)
 #define HIPCHK(expr)                                                                                 \
     do {                                                                                             \
         hipError_t e_ = (expr);                                                                      \
-        if (e_ != hipSuccess) return fail(GV_E_HIP, std::string(#expr) + ": " + hipGetErrorString(e_)); \
+        if (e_ != hipSuccess) {                                                                      \
+            g_oom = e_ == hipErrorOutOfMemory;                                                       \
+            return fail(GV_E_HIP, std::string(#expr) + ": " + hipGetErrorString(e_));                \
+        }                                                                                            \
     } while (0)
 
 double now_ms()
@@ -212,6 +216,7 @@ struct Lib {
     double e_in = 0.0;
     int64_t tracks0[3] = {0, 0, 0};
     bool staged = false;
+    bool prim_there = false;   // the staged primaries are on the device
     bool kept = false;   // device memory of a previous context is still here
     size_t staged_b = 0, staged_e = 0;   // window whose queue slots are on the device
     bool staged_one_queue = false;       // ... laid out for one mixed pool (plain) or per type
@@ -292,16 +297,32 @@ void release_queues()
     L.rk_jcap = 0;
 }
 
-// ensure(), and once more without the queues if the device has no room beside
-// them: they may be another context's, larger than this one needs (the
-// transport makes them again).  Not for buffers made after the queues.
-template <class T> hipError_t ensure_before_queues(DBuf<T>& b, size_t count)
+// All that a transport makes again, besides the queues: deposits, ledger,
+// primaries (from their host copy), status words, and the trace if nothing is in it.
+void release_run_memory()
 {
-    hipError_t e = b.ensure(count);
-    if (e != hipErrorOutOfMemory) return e;
-    (void)hipGetLastError();
     release_queues();
-    return b.ensure(count);
+    L.edep.release();
+    L.ledger.release();
+    L.prim.release();
+    L.prim_there = false;
+    L.prim_slot.release();
+    L.status.release();
+    if (L.stats.trace_records == 0) L.trace.release();
+    L.staged_b = L.staged_e = (size_t)-1;
+}
+
+// f(), and once more without the memory that a transport can make again if the
+// device has no room beside it: it may be a previous context's, and larger than
+// this one needs.
+template <class F> int with_room(F f)
+{
+    g_oom = false;
+    const int rc = f();
+    if (rc != GV_E_HIP || !g_oom) return rc;
+    (void)hipGetLastError();
+    release_run_memory();
+    return f();
 }
 
 void release_all()
@@ -360,7 +381,7 @@ void reset_context()
 {
     const size_t held = L.q64.bytes + L.qmix.bytes + L.rk_jobs.bytes() + L.plain_pool.bytes + L.pl_L.bytes() +
                         L.pl_G.bytes() + L.pl_pr.bytes() + L.pl_o.bytes() + L.edep.bytes() + L.ledger.bytes() +
-                        L.trace.bytes() + L.prim.bytes();
+                        L.trace.bytes() + L.prim.bytes() + L.status.bytes();
     if (held > kKeepBytes) {
         release_all();
         return;
@@ -595,15 +616,15 @@ int ensure_common(int64_t n_events)
     const size_t ne = (size_t)n_events * (size_t)std::max(L.n_cells, 1);
     if (L.edep.n < ne) {
         drop_graph();
-        HIPCHK(ensure_before_queues(L.edep, ne));
+        HIPCHK(L.edep.ensure(ne));
     }
     if (L.ledger.n < (size_t)n_events * 4) {
         drop_graph();
-        HIPCHK(ensure_before_queues(L.ledger, (size_t)n_events * 4));
+        HIPCHK(L.ledger.ensure((size_t)n_events * 4));
     }
     if (L.cfg.trace_cap > 0 && L.trace.n < (size_t)L.cfg.trace_cap) {
         drop_graph();
-        HIPCHK(ensure_before_queues(L.trace, (size_t)L.cfg.trace_cap));
+        HIPCHK(L.trace.ensure((size_t)L.cfg.trace_cap));
     }
     HIPCHK(L.trace_n.ensure(1));
     if (!L.esc_hist.p) {
@@ -615,6 +636,18 @@ int ensure_common(int64_t n_events)
     if (!L.h_mirror) HIPCHK(hipHostMalloc((void**)&L.h_mirror, sizeof(CtrlMirror), hipHostMallocDefault));
     if (!L.ev0) HIPCHK(hipEventCreate(&L.ev0));
     if (!L.ev1) HIPCHK(hipEventCreate(&L.ev1));
+    return GV_OK;
+}
+
+// the staged primaries to the device, if they are not there
+int upload_primaries()
+{
+    if (L.prim_there) return GV_OK;
+    HIPCHK(L.prim.ensure((size_t)L.n_prim));
+    HIPCHK(hipMemcpyAsync(L.prim.p, L.hp.data(), (size_t)L.n_prim * sizeof(PrimDev), hipMemcpyHostToDevice, stream()));
+    HIPCHK(hipStreamSynchronize(stream()));
+    L.staged_b = L.staged_e = (size_t)-1;
+    L.prim_there = true;
     return GV_OK;
 }
 
@@ -1727,7 +1760,7 @@ int gv_init(const gv_material* mats, int32_t n_mats, const gv_geometry* geom, co
     L.phys.fs_alias = L.cfg.fs_alias;
     HIPCHK(hipMemcpyToSymbolAsync(HIP_SYMBOL(c_geom), &L.geom, sizeof(DevGeom), 0, hipMemcpyHostToDevice, stream()));
     HIPCHK(hipMemcpyToSymbolAsync(HIP_SYMBOL(c_phys), &L.phys, sizeof(DevPhys), 0, hipMemcpyHostToDevice, stream()));
-    int rc = build_tables();
+    int rc = with_room(build_tables);
     if (rc) {
         release_all();
         return rc;
@@ -1803,10 +1836,9 @@ int gv_stage(const gv_primary* primaries, int64_t n)
     }
     L.n_events = n_events;
     L.n_prim = n;
-    HIPCHK(ensure_before_queues(L.prim, (size_t)n));
-    HIPCHK(hipMemcpyAsync(L.prim.p, L.hp.data(), (size_t)n * sizeof(PrimDev), hipMemcpyHostToDevice, stream()));
-    HIPCHK(hipStreamSynchronize(stream()));
-    L.staged_b = L.staged_e = (size_t)-1;
+    L.prim_there = false;
+    int rc = with_room(upload_primaries);
+    if (rc) return rc;
     L.staged = true;
     return GV_OK;
 }
@@ -1823,21 +1855,25 @@ int gv_transport_staged(uint64_t seed, double* edep_out)
     struct Guard {
         ~Guard() { L.busy = false; }
     } guard;
-    int rc = ensure_common(n_events);
-    if (rc) return rc;
     hipStream_t s = stream();
-    rc = reset_run_buffers(n_events);
-    if (rc) return rc;
-    L.stats = gv_stats_t{};
-    L.autotune_ms = 0.0;
-    L.tuned = false;
-    L.plain_loads = L.plain_stores = 0.0;
-    L.stats.init_ms = L.init_ms;
-    L.stats.driver = L.cfg.driver;
-    L.stats.precision = L.cfg.precision;
-    if (L.cfg.driver == GV_DRIVER_PLAIN) rc = transport_plain(n_events, seed);
-    else if (L.cfg.precision == GV_P64) rc = transport_batched<P64>(n_events, seed);
-    else rc = transport_batched<PMix>(n_events, seed);
+    int rc = with_room([&]() -> int {
+        L.stats = gv_stats_t{};
+        int e = upload_primaries();
+        if (e) return e;
+        e = ensure_common(n_events);
+        if (e) return e;
+        e = reset_run_buffers(n_events);
+        if (e) return e;
+        L.autotune_ms = 0.0;
+        L.tuned = false;
+        L.plain_loads = L.plain_stores = 0.0;
+        L.stats.init_ms = L.init_ms;
+        L.stats.driver = L.cfg.driver;
+        L.stats.precision = L.cfg.precision;
+        if (L.cfg.driver == GV_DRIVER_PLAIN) return transport_plain(n_events, seed);
+        if (L.cfg.precision == GV_P64) return transport_batched<P64>(n_events, seed);
+        return transport_batched<PMix>(n_events, seed);
+    });
     if (rc) return rc;
     // ---- results ----
     const size_t ne = (size_t)n_events * (size_t)L.n_cells;
