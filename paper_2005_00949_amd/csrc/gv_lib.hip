@@ -47,6 +47,7 @@ int fail(int code, const std::string& msg)
         hipError_t e_ = (expr);                                                                      \
         if (e_ != hipSuccess) {                                                                      \
             g_oom = e_ == hipErrorOutOfMemory;                                                       \
+            (void)hipGetLastError();   /* or the next launch's check would report it again */        \
             return fail(GV_E_HIP, std::string(#expr) + ": " + hipGetErrorString(e_));                \
         }                                                                                            \
     } while (0)
@@ -320,7 +321,6 @@ template <class F> int with_room(F f)
     g_oom = false;
     const int rc = f();
     if (rc != GV_E_HIP || !g_oom) return rc;
-    (void)hipGetLastError();
     release_run_memory();
     return f();
 }

@@ -69,3 +69,16 @@ def test_queues_find_room_beside_kept_deposits(hip, precision):
     finally:
         assert hip.hipFree(block) == 0
         eng.close()
+
+
+def test_a_call_that_finds_no_room_fails_alone(hip):
+    """Queues of 2^30 slots have no room on any card; the next call succeeds."""
+    import paper_2005_00949_amd as gv
+    eng, want = _small(gv)
+    eng.configure(capacity=1 << 30)
+    prim = gv_inputs.mixed_beam(200, 3, 30.0, 300.0)
+    with pytest.raises(gv.GvError, match="out of memory"):
+        eng.transport(prim, 42)
+    eng.configure(capacity=0)
+    assert np.array_equal(np.asarray(eng.transport(prim, 42)), want)
+    eng.close()
