@@ -644,7 +644,8 @@ struct Ctrl {
     uint32_t count[2][4];   // queue sizes by buffer parity and type
     uint32_t ticket;        // next basket to claim
     uint32_t epoch;         // launch counter tagging look-back status words
-    uint32_t overflow;      // bit 0: a queue ran out of capacity; bit 1: a look-back wait gave up
+    uint32_t overflow;      // bit 0: a queue ran out of capacity; bit 1: a look-back wait gave up;
+                            // bit 2: a pool's tags and counts disagree
     uint32_t done;          // workgroups finished in this launch
     uint32_t halt;          // overflow as seen at the end of the previous launch
     uint32_t n_vac;         // pool kernel: charged tracks in vacuum among this launch's outputs

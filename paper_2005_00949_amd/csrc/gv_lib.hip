@@ -687,11 +687,13 @@ Sinks make_sinks()
 }
 
 // Launches one event window may take before the driver reports a stuck loop.
-// Every launch moves every live track by at least one step and a track ends
-// within max_steps_per_track + 1 launches, but each secondary starts again at
-// step 0, so the bound allows a tree of secondaries kMaxGenerations deep (no
-// electromagnetic shower of these energies comes near it); it is also capped
-// so that the look-back epoch cannot wrap inside a window.
+// Every launch of the step kernel moves every live track by at least one step; one of
+// the pool kernel takes every wavefront's fullest basket through a stage of steps, and
+// a wavefront's input is at most 64 tracks of one type (but for the few that take a
+// second chunk).  A track ends within max_steps_per_track + 1 such launches, but each
+// secondary starts again at step 0, so the bound allows a tree of secondaries
+// kMaxGenerations deep (no electromagnetic shower of these energies comes near it);
+// it is also capped so that the look-back epoch cannot wrap inside a window.
 constexpr uint32_t kEpochMask = (1u << 30) - 1u;
 constexpr int64_t kMaxWindowLaunches = (int64_t)1 << 26;
 constexpr int64_t kMaxGenerations = 256;
@@ -1255,6 +1257,7 @@ int run_pool_window(size_t b, size_t e, uint64_t seed, const Tuning& tu, BulkRat
         L.stats.iterations += K;
         L.stats.graph_replays += bulk ? 1 : 0;
         launches += K;
+        if (m.overflow & 4u) return fail(GV_E_STATE, "pool kernel: the tags and counts of a pool disagree");
         if (m.overflow & 2u) return fail(GV_E_STATE, "compaction look-back wait exceeded its bound");
         if (m.overflow) return GV_E_CAPACITY;
         if (L.progress)

@@ -660,7 +660,7 @@ __global__ void __launch_bounds__(kPoolBlock, PoolSize<P>::wgs(INTEG)) k_pool(Po
         const int what = pool_take(M, st, lane, drain, input, (int)chunk, tag, n, slot);
         if (what == kTakeNone) break;
         if (n == 0) {   // tags and counts disagree: report it instead of going round for ever
-            if (lane == 0) atomicOr(&pool_args<P>().ctrl->overflow, 2u);
+            if (lane == 0) atomicOr(&pool_args<P>().ctrl->overflow, 4u);
             break;
         }
         if (what == kTakeInput) {
