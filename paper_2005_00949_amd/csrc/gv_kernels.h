@@ -85,7 +85,7 @@ __device__ __forceinline__ void store_child(const Soa<P>& q, size_t i, const Tra
 // global counters (gv_stats)
 enum : int { kCSteps = 0, kCTracks = 3, kCProc = 6, kCEscaped = 14, kCKilled = 15, kCRej = 16, kCLoads = 17,
              kCStores = 18, kCRkSub = 19, kCRkRej = 20, kCRkSlots = 21, kCLaneSlots = 22, kCHelperSteps = 23,
-             kCRkParked = 24, kNCount = 25 };
+             kCRkParked = 24, kCPoolSpills = 25, kNCount = 26 };
 
 // per-lane sums of the adaptive-integration tallies over one launch
 struct RkSum {
@@ -761,7 +761,7 @@ struct CtrlMirror {
     uint32_t count[3];          // tracks queued for the next launch, by type
     uint32_t n_vac;             // of them, charged tracks in vacuum
     uint32_t overflow;
-    uint32_t pad;
+    uint32_t spills;            // secondaries the transport has queued so far for want of a free slot
     unsigned long long steps;   // steps of the transport so far
 };
 
@@ -792,6 +792,8 @@ __device__ __forceinline__ void finish_launch(Ctrl* ctrl, int parity, uint32_t p
                 for (int t = 0; t < 3; ++t)
                     steps += __hip_atomic_load(&counters[kCSteps + t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 mirror->steps = steps;
+                mirror->spills = (uint32_t)__hip_atomic_load(&counters[kCPoolSpills], __ATOMIC_RELAXED,
+                                                             __HIP_MEMORY_SCOPE_AGENT);
                 ctrl->n_vac = 0;
             }
             ctrl->count[parity][0] = 0;

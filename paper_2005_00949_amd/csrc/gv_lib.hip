@@ -1194,6 +1194,7 @@ int run_pool_window(size_t b, size_t e, uint64_t seed, const Tuning& tu, BulkRat
     uint32_t n_gamma = counts[0];
     bool grew = true, in_tail = false;
     unsigned long long steps = 0;
+    uint32_t spills = 0;
     int64_t launches = 0;
     const int64_t bound = window_launch_bound();
     int64_t tail_steps0 = 0;
@@ -1245,6 +1246,7 @@ int run_pool_window(size_t b, size_t e, uint64_t seed, const Tuning& tu, BulkRat
             m.n_vac = loopers && m.count[0] == 0 && left <= n ? left : 0;
             m.overflow = L.h_ctrl->overflow;
             m.steps = c3[0] + c3[1] + c3[2];
+            m.spills = spills;
         } else {
             HIPCHK(hipStreamSynchronize(s));
         }
@@ -1261,9 +1263,9 @@ int run_pool_window(size_t b, size_t e, uint64_t seed, const Tuning& tu, BulkRat
         if (m.overflow & 2u) return fail(GV_E_STATE, "compaction look-back wait exceeded its bound");
         if (m.overflow) return GV_E_CAPACITY;
         if (L.progress)
-            std::fprintf(stderr, "[gv] %s%s%s: %.3f ms, population %u/%u/%u, vacuum %u, steps %llu\n",
-                         bulk ? "bulk" : step_kernel ? "loopers" : "pool", helper ? " helper" : "", tail ? " tail" : "", ms, m.count[0], m.count[1],
-                         m.count[2], m.n_vac, m.steps - steps);
+            std::fprintf(stderr, "[gv] %s%s%s: %.3f ms, population %u/%u/%u, vacuum %u, steps %llu, spilled %u\n",
+                         bulk ? "bulk" : step_kernel ? "loopers" : "pool", helper ? " helper" : "", tail ? " tail" : "",
+                         ms, m.count[0], m.count[1], m.count[2], m.n_vac, m.steps - steps, m.spills - spills);
         if (bulk && bulk_only) {
             bulk_only->ms += ms;
             bulk_only->steps += m.steps - steps;
@@ -1271,6 +1273,7 @@ int run_pool_window(size_t b, size_t e, uint64_t seed, const Tuning& tu, BulkRat
             if (bulk_only->behind()) return GV_OK;
         }
         steps = m.steps;
+        spills = m.spills;
         n_gamma = m.count[0];
         n_vac = m.n_vac;
         grew = m.count[0] + m.count[1] + m.count[2] > n;

@@ -553,7 +553,10 @@ __device__ __forceinline__ void pool_interact(PoolMem<P>& M, PoolState& st, uint
             if (!m) continue;
             const int leader = __ffsll((unsigned long long)m) - 1;
             uint32_t base = 0;
-            if (lane == leader) base = atomicAdd(&A.ctrl->count[A.parity ^ 1][q], (uint32_t)__popcll(m));
+            if (lane == leader) {
+                base = atomicAdd(&A.ctrl->count[A.parity ^ 1][q], (uint32_t)__popcll(m));
+                atomicAdd(&cnt[kCPoolSpills], (unsigned)__popcll(m));
+            }
             base = (uint32_t)__shfl((int)base, leader, 64);
             if (spill && qt == q) {
                 const uint32_t pos = base + (uint32_t)mbcnt64(m);
