@@ -2066,7 +2066,7 @@ int gv_compact3_noalloc(const int8_t* codes, int64_t n, int32_t block, int32_t* 
     }
     hipStream_t s = (hipStream_t)hip_stream;
     // 16-byte loads need the codes 16-byte aligned, word loads 4-byte; codes at
-    // any other address are read byte by byte
+    // any other address are read in words that do not begin with an input
     const uintptr_t at = (uintptr_t)codes;
     if (n == 0) k_na_clear<<<1, 64, 0, s>>>(counts);
     else if (n >= kNaManyInputs && at % 16 == 0) launch_part<16, true>(codes, n, index, counts, totals, s);

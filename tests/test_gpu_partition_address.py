@@ -1,0 +1,67 @@
+"""The allocation-free compaction of codes that begin at any address: against numpy's
+stable partition around the edges of its blocks and of one launch, between bytes that
+are no codes; and the time of an odd address beside that of an aligned one."""
+import time
+
+import numpy as np
+import pytest
+
+from gvtest import stable_partition_reference
+
+pytestmark = pytest.mark.gpu
+
+
+def _call(gv, torch, buf, off, n):
+    index = torch.full((9 * max(n, 1),), -7, dtype=torch.int32, device="cuda")
+    counts = torch.full((4,), 9, dtype=torch.int32, device="cuda")
+    stream = torch.cuda.current_stream().cuda_stream
+    gv.compact3_noalloc(buf.data_ptr() + off, n, 256, index.data_ptr(), counts.data_ptr(), stream)
+    torch.cuda.synchronize()
+    return index.cpu().numpy().reshape(3, -1), counts.cpu().numpy()
+
+
+@pytest.mark.parametrize("off", [1, 2, 3, 4, 6, 8, 13])
+def test_codes_at_any_address(off):
+    import torch
+
+    import paper_2005_00949_amd as gv
+    rng = np.random.default_rng(off)
+    for n in (1, 2, 3, 4, 5, 6, 7, 8, 9, 15, 16, 17, 18, 255, 1023, 1024, 1025, 1026, 4099, 8191, 8192, 8193, 100003,
+              (1 << 20) - 1, 1 << 20, (1 << 20) + 1, (1 << 20) + 17):
+        codes = rng.integers(-1, 3, 3 * n).astype(np.int8)
+        host = np.full(3 * n + 64, 77, dtype=np.int8)      # 77 is no code: it would be counted as an error
+        host[off:off + 3 * n] = codes
+        index, counts = _call(gv, torch, torch.from_numpy(host).cuda(), off, n)
+        assert counts[3] == 0, n
+        if n <= 100003:
+            want = stable_partition_reference(codes)
+        else:
+            at = [np.flatnonzero(codes == q) for q in range(3)]
+            want = [(a // 3 * 4 + a % 3).astype(np.int32) for a in at]
+        for q in range(3):
+            assert counts[q] == len(want[q]) and np.array_equal(index[q, :counts[q]], want[q]), (n, q)
+
+
+@pytest.mark.parametrize("n", [5000, 8192])
+def test_an_odd_address_costs_no_more(n):
+    """A word more to load and a shift per word, of a call that is bound by its launch;
+    byte loads took 1.4 and 1.6 times as long."""
+    import torch
+
+    import paper_2005_00949_amd as gv
+    buf = torch.zeros(3 * n + 64, dtype=torch.int8, device="cuda")
+    index = torch.empty(9 * n, dtype=torch.int32, device="cuda")
+    counts = torch.empty(4, dtype=torch.int32, device="cuda")
+    us = {}
+    for off in (0, 1):
+        best = 1e9
+        for _ in range(10):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            for _ in range(100):
+                gv.compact3_noalloc(buf.data_ptr() + off, n, 256, index.data_ptr(), counts.data_ptr())
+            torch.cuda.synchronize()
+            best = min(best, (time.perf_counter() - t) * 1e4)
+        us[off] = best
+    print(f"\n{n} inputs: {us[0]:.2f} us aligned, {us[1]:.2f} us at an odd address")
+    assert us[1] < 1.25 * us[0]
