@@ -78,7 +78,9 @@ enum { GV_MAP_UNIFORM = 0, GV_MAP_SOLENOID = 1 };
  * order of the input slots (single-pass look-back over the claimed baskets),
  * identical in every run.  Populations too small to fill the GPU, of
  * transports that leave every knob at 0 and record no steps, are followed in
- * on-chip pools instead, which have no such order.  Results are the same in
+ * on-chip pools instead, which have no such order, and a launch of theirs ends by
+ * the clock: launches, slots moved and lane slots then differ from run to run in
+ * either order.  Results are the same in
  * all: a track's random numbers are keyed by (event, track id, step), never by
  * its queue slot. */
 enum { GV_ORDER_ARRIVAL = 0, GV_ORDER_STABLE = 1 };
@@ -206,31 +208,38 @@ typedef struct {
     int64_t interactions[8];        /* compton, pair, moller, bhabha, brems e-, brems e+,
                                        annihilation at rest, null (empty sampling interval) */
     int64_t escaped, killed, rejection_exhausted;
-    int64_t iterations;             /* step launches */
-    int64_t graph_replays;
+    int64_t iterations;             /* launches of the step and pool kernels */
+    int64_t graph_replays;          /* of the step kernel's graphs: without the pool kernel every
+                                       launch belongs to one, with it those of populations that
+                                       fill the GPU */
     int64_t trace_records;
     int64_t overflow_restarts;
     double e_in, e_dep, e_escaped, e_killed;   /* MeV, all events */
     double n_pair, n_annih;
     double transport_ms;            /* wall time of gv_transport */
     double init_ms;                 /* wall time of gv_init (tables, uploads) */
-    double kernel_ms;               /* summed duration of the step kernels (HIP events) */
-    int64_t kernel_launches;        /* step-kernel launches timed into kernel_ms */
+    double kernel_ms;               /* summed duration of the step and pool kernels and the vacuum
+                                       helper (HIP events) */
+    int64_t kernel_launches;        /* step- and pool-kernel launches timed into kernel_ms */
     double alg_bytes;               /* algorithmic track-state bytes: per step one slot read
                                        and the moving fields written back (PMix 60 + 48 B,
                                        FP64 77 + 64 B), plus one slot per secondary */
-    int32_t driver, precision, basket, occupancy, inner_steps, graph_steps;
+    int32_t driver, precision;
+    int32_t basket, occupancy, inner_steps, graph_steps;   /* the step kernel's knobs, also where
+                                       the pool kernel, which has none, took every track */
     int64_t capacity;
-    double state_bytes;             /* track-state bytes the step kernels actually moved
+    double state_bytes;             /* track-state bytes the step and pool kernels actually moved
                                        (slot reads + slot writes) */
     double autotune_ms;             /* time spent choosing basket/occupancy/inner steps
                                        before this transport (0 if a cached choice was used) */
     int32_t tuned;                  /* 1: basket/occupancy/inner steps left at 0 were set by
-                                       the autotuner, 0: defaults or caller's values */
-    int32_t queue_order;
+                                       the autotuner, 0: defaults or caller's values (defaults
+                                       also where the autotuner's sample had no step-kernel work) */
+    int32_t queue_order;            /* as configured; it is the step kernel's, the pool kernel's
+                                       tracks have no order */
     int32_t reserved;
-    double tail_kernel_ms;          /* part of kernel_ms spent in the tail replays (batched
-                                       driver): after the population peaked and fell below the
+    double tail_kernel_ms;          /* part of kernel_ms spent in the tail (batched driver; tail
+                                       replays, or the pool kernel's launches): after the population peaked and fell below the
                                        tail threshold, or, in a window whose population never
                                        reaches the threshold, once a replay no longer raised it */
     int64_t rk_substeps;            /* RK45: accepted substeps */
@@ -242,11 +251,13 @@ typedef struct {
                                        1 - (substeps + rejected) / lane_slots is the fraction
                                        of idle lanes in the integration loop */
     int64_t lane_slots;             /* batched driver: 64 x (step-loop iterations) summed over the
-                                       wavefronts of every basket, a wavefront running as many
-                                       iterations as its busiest lane; total steps / lane_slots is
+                                       wavefronts of every basket (pool kernel: of every stage),
+                                       a wavefront running as many iterations as its busiest lane;
+                                       total steps / lane_slots is
                                        the lane use of the stepping loop (0 for the plain driver) */
     int64_t tail_steps;             /* steps taken in the launches counted in tail_kernel_ms */
-    int64_t helper_steps;           /* of those, steps taken by the tail's vacuum helper kernel */
+    int64_t helper_steps;           /* steps taken by the vacuum helper kernel, in the tail unless
+                                       a batch begins with loopers alone */
     int64_t rk_parked;              /* RK45 with arrival order: charged steps parked at their move
                                        in the integration queue (Sec. 3.6: lanes refilled as
                                        integrations finish); the rest integrate inside the step */

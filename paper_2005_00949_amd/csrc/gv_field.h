@@ -23,8 +23,10 @@ enum : int { kFieldHelix = 0, kFieldRk4 = 1, kFieldRk45 = 2 };
 
 // sqrt(x) for x in [2^-700, 2^1000] and n / d for |d| in [2^-500, 2^500], |n|
 // below 2^500 (and above 2^-500 or so small that n / d counts for nothing): the
-// sequences the compiler expands sqrt and division into, which are correct to
-// the last bit, less the scaling that only numbers outside these ranges need.
+// sequences into which the compiler (the open-source AMDGPU backend of LLVM)
+// expands double sqrt and division, which are correct to the last bit, less the
+// scaling that only numbers outside these ranges need.  The order of operations is
+// theirs, so that the bits are.
 // root: Newton-Goldschmidt iteration of the reciprocal root with residual
 // corrections.  recip: two Newton steps; quot: one residual correction.
 __device__ __forceinline__ double root(double x)

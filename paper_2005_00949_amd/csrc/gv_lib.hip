@@ -1060,15 +1060,14 @@ template <class P> int run_batched_window(size_t b, size_t e, uint64_t seed, con
 
 // ---- the pool kernel's driver ----------------------------------------------
 
-// Time a wavefront takes per launch, from its start, unless its input lasts longer
-// (microseconds):
-// longer, and wavefronts that have emptied their pools wait for the others;
-// shorter, and launches and their read-backs (~25 us) weigh more (1000 x 10 GeV
-// e-: 17.2 / 16.5 / 16.2 ms at 50 / 100 / 200 us; 100 x 50 GeV with RK45: 115 /
-// 106 / 111 ms).  And steps a track takes per stage: 4 to 8 measured alike, 2
-// and 16 slower; with an integrator, whose steps may take a hundred times
-// longer, fewer.
-constexpr int kPoolBudget = 100;
+// Time after which a wavefront begins no stage, from its start, unless its input lasts
+// longer (microseconds): longer, and wavefronts that have emptied their pools wait for
+// the others; shorter, and launches and their read-backs (~25 us) weigh more (at 80 /
+// 120 / 140 / 170 us: one 1 GeV e- 1.05 / 1.04 / 1.10 / 1.12 ms, 1,000 of 10 GeV 14.9 /
+// 14.8 / 14.6 / 14.4, 100 x 5 GeV in the field map 9.4 / 8.5 / 8.2 / 8.0).  And steps a
+// track takes per stage: 4 to 8 measured alike, 2 and 16 slower; with an integrator,
+// whose steps may take a hundred times longer, fewer.
+constexpr int kPoolBudget = 130;
 constexpr int kPoolInner = 8;
 constexpr int kPoolInnerInteg = 2;
 // vacuum steps per track and helper launch between two pool launches
@@ -1126,7 +1125,7 @@ template <class P> void launch_pool_helper(int parity, uint32_t n, hipStream_t s
 // Loopers alone, more of them than the helper takes: the step kernel as the tail
 // graph launches it, up to 256 steps per track and launch, its wavefronts full.
 // The pool kernel would give each wavefront a few of them and stop them every
-// 100 us, that is 50 steps or, with an integrator, 5 (20,000 loopers of 20,000 steps
+// 130 us, that is 70 steps or, with an integrator, 5 (20,000 loopers of 20,000 steps
 // in a uniform field: 66 ms there, 36 ms here; 1,500 with RK45 in the field map, 3,000
 // steps: 426 and 110 ms).  An even number of launches, so that they end at parity
 // 0.
