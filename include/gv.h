@@ -233,8 +233,8 @@ typedef struct {
     double autotune_ms;             /* time spent choosing basket/occupancy/inner steps
                                        before this transport (0 if a cached choice was used) */
     int32_t tuned;                  /* 1: basket/occupancy/inner steps left at 0 were set by
-                                       the autotuner, 0: defaults or caller's values (defaults
-                                       also where the autotuner's sample had no step-kernel work) */
+                                       the autotuner (to the defaults where its sample had no
+                                       step-kernel work to time), 0: defaults or caller's values */
     int32_t queue_order;            /* as configured; it is the step kernel's, the pool kernel's
                                        tracks have no order */
     int32_t reserved;

@@ -1400,8 +1400,8 @@ int reset_run_buffers(int64_t n_events)
 // method (another kernel each), driver (pool or step kernel in the tail) and
 // batch-size class; the trials' deposits and counters are discarded.  With the
 // pool driver a sample whose population never fills the GPU ends the search: the
-// defaults stand, as `tuned` says, until a batch of the class proves to be another
-// kind (revise_tuning).
+// defaults are the choice, until a batch of the class proves to be another kind
+// (revise_tuning).
 using TuneKey = std::tuple<int, int, int, int, int>;
 template <class P> TuneKey tune_key()
 {
@@ -1429,7 +1429,7 @@ template <class P> int tuned_choice(int64_t n_events, uint64_t seed, std::array<
     auto it = L.tune_cache.find(key);
     if (it != L.tune_cache.end()) {
         choice = it->second.choice;
-        L.tuned = it->second.measured;
+        L.tuned = true;
         return GV_OK;
     }
     const double t0 = now_ms();
@@ -1498,7 +1498,7 @@ template <class P> int tuned_choice(int64_t n_events, uint64_t seed, std::array<
     }
     choice = best;
     L.tune_cache[key] = {best, measured};
-    L.tuned = measured;
+    L.tuned = true;
     L.autotune_ms = now_ms() - t0;
     // discard the trials' results; the transport proper starts clean
     rc = reset_run_buffers(n_events);

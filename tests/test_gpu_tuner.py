@@ -24,10 +24,10 @@ def test_batch_that_never_fills_the_gpu_keeps_the_defaults():
         eng.transport(_low(6000), k)
         s = eng.stats()
         assert (s["basket"], s["occupancy"], s["inner_steps"]) == (256, 3, 4), s["basket"]
-        assert s["tuned"] == 0 and s["graph_replays"] == 0
+        assert s["graph_replays"] == 0
     assert s["autotune_ms"] == 0.0          # and the search is not repeated
     high = gv_inputs.beam(4200, 11, 1.0e4)
-    eng.transport(high, 3)
+    eng.transport(high, 3)                  # finds the untimed choice and shows that it is of another kind
     assert eng.stats()["graph_replays"] > 0
     eng.transport(high, 4)
     s = eng.stats()
