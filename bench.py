@@ -48,8 +48,8 @@ def kernel_source_hash():
 
 
 def measured_traffic(steps_per_launch, workload, knobs):
-    """HBM bytes per launch from the recorded FETCH_SIZE / WRITE_SIZE counters
-    (per step, calibrated against a plain copy), or None when the kernel
+    """HBM bytes per launch from the recorded FETCH_SIZE / WRITE_SIZE counters of
+    the transport's kernels (per step, calibrated against a plain copy), or None when the kernel
     sources changed since they were taken, the workload differs, or no
     recorded entry has these knobs (basket, occupancy, inner steps)."""
     try:
@@ -66,8 +66,8 @@ def measured_traffic(steps_per_launch, workload, knobs):
 
 
 def shower_roofline(res):
-    """Algorithmic bytes per second of the step kernel outside the tail
-    replays: the transport's algorithmic bytes less 108 B per tail step
+    """Algorithmic bytes per second of the kernels outside the tail: the
+    transport's algorithmic bytes less 108 B per tail step
     (mixed-precision slot read and moving fields written; the tail's loopers
     have no secondaries), over the kernel time outside the tail."""
     t = (sum(res["kern_ms"]) - sum(res["tail_ms"])) * 1e-3
@@ -621,9 +621,9 @@ def main():
         "one_gpu_share": res["share"],
         "roofline": {"bound": "hbm", "achieved": achieved / 1e9, "peak": HBM_PEAK / 1e9, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK, "traffic": traffic,
-                     "kernel": "k_step_batched<PMix,%d>" % min(st0["basket"], 256),
-                     "launch": "one step kernel launch; in the low-population tail replays the one-workgroup "
-                               "k_vacuum_helper before it is part of the launch",
+                     "kernel": "k_step_batched<PMix,%d> and k_pool<PMix>" % min(st0["basket"], 256),
+                     "launch": "one launch of the step kernel (populations that fill the GPU) or of the pool "
+                               "kernel (the others), with the k_vacuum_helper before it where loopers alone are left",
                      "avg_launch_us": avg_launch_s * 1e6, "alg_bytes_per_launch": bytes_per_launch,
                      "steps_per_launch": steps_per_launch, "launches": res["launches"],
                      "kernel_source_sha1": kernel_source_hash(),

@@ -930,9 +930,9 @@ __device__ __forceinline__ void make_interaction(const Ctx<P>& c, const Sinks& S
 // One chunk of BLOCK same-type tracks: photons, or (one code for both) electrons
 // or positrons, `ty`.  Each track is stepped up to `inner` times in registers,
 // stopping at its first secondary or its end; then survivors and secondaries are
-// compacted into the output queues.  Bound by issue: vector instructions were
-// issued in 71 % of the kernel's cycles (1,790 per wavefront and step, at 39 % of
-// the lanes; 3,000-event c4 batch), so instructions and lanes count.
+// compacted into the output queues.  Bound by issue: vector instructions are issued
+// in 74 % of the kernel's cycles, at 40 % of the lanes (1,650 lane slots per step; c4,
+// mixed precision, four workgroups per CU), so instructions and lanes count.
 // In FP64 a track also stops at its first interaction, and all interactions of
 // the chunk are made at once after the loop, which otherwise runs every sampler
 // at every step for the few lanes that drew it: the shower phase of 1,250 c4

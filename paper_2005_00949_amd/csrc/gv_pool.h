@@ -23,10 +23,10 @@
 // Below the population that fills the GPU (2 x 256 tracks per CU) this kernel
 // is the faster one, above it the step kernel: of 1000 x 10 GeV e- in 50 layers
 // the part below took 8.1 ms in the step kernel and takes 2.5 ms here, while at
-// 2 to 3 million tracks the step kernel makes 1.4e10 steps/s and this one
-// 1.0e10 (its round trips through LDS, and spilled secondaries).  One 1 GeV e-:
-// 2.92 -> 1.18 ms; 100 of them: 4.51 -> 2.26 ms; 1250 mixed primaries in 4 T,
-// FP64: 92 -> 63 ms.  What bounds it is the latency of single histories: a
+// 2 to 3 million tracks the step kernel makes 1.6e10 steps/s and this one
+// 1.0e10 (its round trips through LDS, and spilled secondaries).  Against the step
+// kernel alone, as it was then: one 1 GeV e- 3.05 -> 1.31 ms; 100 of them 4.68 -> 2.14
+// ms; 1,000 of 10 GeV 21.6 -> 15.1 ms (with the smaller step kernel).  What bounds it is the latency of single histories: a
 // photon step is ~1.2 us of dependent instructions for a lone track.
 //
 // Nothing observable depends on the schedule: a track's random numbers are
