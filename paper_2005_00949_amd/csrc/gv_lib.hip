@@ -1454,6 +1454,7 @@ template <class P> int tuned_choice(int64_t n_events, uint64_t seed, std::array<
         bulk_ran |= rc == GV_E_CAPACITY || bulk.steps > 0;
         if (rc == GV_E_CAPACITY) {
             rate = 0.0;
+            bulk = BulkRate{};   // (no other trial is behind one that did not end)
             return GV_OK;
         }
         if (rc) return rc;
